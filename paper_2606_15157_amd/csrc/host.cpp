@@ -224,7 +224,7 @@ PrefillWorkspace prefill_workspace_layout(int n_jobs, int n_slices, int rows, in
   // the window rows kernel's partial row sums; the first is never smaller where both could run
   w.stats = off;
   const bool pipe_layout = rows == kPipeRows && n_slices <= kPipeMaxSlices;
-  const int parts = window_parts(n_jobs - n_full_jobs - n_tova_jobs, n_slices, rows);
+  const int parts = window_parts_room(n_jobs - n_full_jobs - n_tova_jobs, n_slices, rows);
   const size_t stat_floats = pipe_layout ? (size_t)n_jobs * n_slices * kPipeRows
                                          : (parts > 1 ? (size_t)n_jobs * parts * rows : 0);
   off = round_up(off + sizeof(float) * stat_floats, 256);
@@ -652,6 +652,7 @@ int rkv_prefill_evict(const rkv_plan* plan, const rkv_shape* shape, const rkv_pr
     rkv::PrefillWorkspace W = rkv::prefill_workspace_layout(n_jobs, P.n_slices, ktiles * 32, L, G, P.pool_half,
                                                             n_full_jobs, n_tova_jobs);
     P.window_parts = rkv::window_parts(n_jobs - n_full_jobs - n_tova_jobs, P.n_slices, ktiles * 32);
+    P.window_ranges = rkv::window_split(std::max(1, n_jobs - n_full_jobs - n_tova_jobs), P.n_slices, 64, 2);
     char* base = (char*)ws;
     P.counters = (uint32_t*)(base + W.counters);
     P.stats = (float*)(base + W.stats);

@@ -59,13 +59,8 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // for all memory operations (earlier stores included) before every one of those stores.
 __device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xf << 8)); }
 
-// Zeroes the counters (the status word at counters[0] only in the call's first launch group, so
-// that it covers the whole call) before the window scoring kernels.
-__global__ void reset_counters(uint32_t* counters, int n, int clear_status) {
-  const int i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-  for (int i = i0; i < n; i += stride)
-    if (i > 0 || clear_status) counters[i] = 0u;
-}
+// Clears the call's status word where no window-scored job's first kernel does it.
+__global__ void reset_status(uint32_t* counters) { counters[0] = 0u; }
 
 // ---------------------------------------------------------------------------------------------
 // Cross-lane sums over the 32 window rows held by the lanes of each half-wave.
@@ -1493,11 +1488,8 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
     if (ntg == 1) launch_staged(kStageZero, prepare_kernel<1>, prep_grid, prep_block, 0, st, P);
     else if (ntg == 2) launch_staged(kStageZero, prepare_kernel<2>, prep_grid, prep_block, 0, st, P);
     else launch_staged(kStageZero, prepare_kernel<4>, prep_grid, prep_block, 0, st, P);
-  } else {
-    // the status word is cleared even without jobs
-    const int n_cnt = kCounterStride * (1 + n_jobs);
-    const int blocks = std::max(1, std::min(64, (n_cnt + 255) / 256));
-    launch_staged(kStageZero, reset_counters, dim3(blocks), dim3(256), 0, st, P.counters, n_cnt, (int)P.first_group);
+  } else if (n_jobs == 0 && P.first_group) {
+    launch_staged(kStageZero, reset_status, dim3(1), dim3(1), 0, st, P.counters);
   }
   if (n_jobs > 0) {
     if (pipe) {

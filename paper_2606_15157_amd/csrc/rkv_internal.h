@@ -61,8 +61,10 @@ struct PrefillLaunch {
   float scale_log2;       // log2(e) / sqrt(d)
   int32_t force_window;   // test hook: the window kernels even where the pipelined one applies
   int32_t window_parts;   // window rows kernel: workgroups (key ranges) per job
+  int32_t window_ranges;  // window columns kernel: likewise
   // workspace regions
-  uint32_t* counters;     // [0] status; job j's slice-arrival counter at [kCounterStride * (1 + j)]
+  uint32_t* counters;     // [0] status; job j's line at [kCounterStride * (1 + j)]: word 1 its repair flag,
+                          // from word 2 the overflow marks of the window rows kernel's parts
   float* stats;           // [J][n_slices][128]  pipelined kernel: per-slice row sums (NaN until stored);
                           // [J][window_parts][R]  window kernels with several parts: partial row sums
   float* part;            // [J][kPipeGroups][128]  pipelined kernel: per-group sums of those (NaN until stored)
@@ -92,10 +94,24 @@ constexpr int kPipeRows = 128;      // window rows of a job in the pipelined sco
 constexpr int kPipeMaxSlices = 64;  // slices per job it takes
 constexpr int kPipeGroups = 8;      // slice groups per job of its two-level row-sum exchange
 
-// Key ranges per job of the window rows kernel: with few jobs, enough workgroups to fill the
-// chip (two resident per CU at four row tiles, one at eight); at most 8 parts of at least 8
-// slices each.  The host's workspace layout and launch both take it from here.
-inline int window_parts(int n_window_jobs, int n_slices, int rows) {
+// Ways to cut each of n_jobs jobs of `units` 128-key slices, 1 .. most: the fewest slice times until
+// the last of the workgroups is done, with 512 of them resident (two per CU) and `lead` slice times
+// spent by each before its first slice (queries, references or normalisers, the first tiles).
+inline int window_split(int n_jobs, int units, int most, int lead) {
+  int best = 1;
+  int64_t best_cost = INT64_MAX;
+  for (int p = 1; p <= most && p <= units; ++p) {
+    const int64_t cost = (((int64_t)n_jobs * p + 511) / 512) * ((units + p - 1) / p + lead);
+    if (cost < best_cost) {
+      best = p;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+// Partial row sums per row the workspace holds for the window rows kernel (jobs few enough to leave
+// the chip idle; at most 8, of at least 8 slices each).
+inline int window_parts_room(int n_window_jobs, int n_slices, int rows) {
   if (n_window_jobs <= 0) return 1;
   const int want = rows <= 4 * 32 ? 512 : 256;
   int p = (want + n_window_jobs - 1) / n_window_jobs;
@@ -103,6 +119,12 @@ inline int window_parts(int n_window_jobs, int n_slices, int rows) {
   const int by_len = n_slices / 8 > 1 ? n_slices / 8 : 1;
   p = p < by_len ? p : by_len;
   return p > 1 ? p : 1;
+}
+// Key ranges per job of the window rows kernel.  The sums of one more part than the room fit, since
+// several parts leave the row normalisers that follow it unused.
+inline int window_parts(int n_window_jobs, int n_slices, int rows) {
+  const int room = window_parts_room(n_window_jobs, n_slices, rows);
+  return room == 1 ? 1 : window_split(n_window_jobs, n_slices, room + 1, 3);
 }
 
 // Error reporting (thread-local last error).

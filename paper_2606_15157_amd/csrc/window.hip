@@ -2,54 +2,50 @@
 // keys per job, or eight row tiles: G * ceil(w / 32) > 4) on gfx950.  Per (sequence, layer, KV
 // head) job the scores are those of the pipelined kernel (Section 2.1's SnapKV and H2O rules):
 //   A[g][j] = sum_i softmax_j(Q[g,i] . K[j] / sqrt(d)), S = mean_g maxpool(A[g]) or mean_g A[g],
-// computed in two passes over the keys instead of one pass with a cross-workgroup exchange:
+// computed in two passes over the keys instead of one pass with a cross-workgroup exchange.
+//
+// Both passes (four waves; tile32.h) hold 64 of the job's R = 32 NRT window rows (the rows of every
+// head of the group, padded) per wave in registers and stream the keys through LDS in 64-key tiles:
+// with eight row tiles the four waves take a quarter of the rows each, with four row tiles wave wv
+// takes row half wv % 2 and key half wv / 2 of a tile.  The MFMAs of a 32-key subtile run beside the
+// exponentials of the one before, across tiles too; tiles with masked pairs only overwrite the
+// masked logits in between.
 //
 // window_rows_kernel<NRT>: one workgroup per job (per part of its keys when there are few jobs:
-//   the columns kernel then adds the parts' row sums), one wave per 32 window rows (R = 32 NRT
-//   rows, the query rows of every head of the group, padded).  The wave's query fragments stay in
-//   registers; 128-key tiles stream through two LDS buffers (LDS DMA, one tile ahead) and bf16
-//   MFMA logits are taken against a fixed per-row reference c_r = max(logit with the row's own
-//   key, logit with key 0), both true logits of the row; each lane sums e =
-//   exp2((z - c_r) log2(e) / sqrt(d)) over its keys.  The row's log2 normaliser Lambda_r = c_r
-//   log2(e)/sqrt(d) + log2(Z_r) goes to the workspace; a row whose sum overflows (a key more than
-//   ~88 natural-log units above its reference) flags the job for the exact rescoring of the
-//   selection kernels.  On tiles without masks the MFMAs of one half-tile run interleaved with
-//   the exponentials of the other half.
-// window_cols_kernel<NRT>: one workgroup per (job, 32 consecutive 128-key blocks); the job's
-//   query block and normalisers sit in LDS, each of the four waves keeps its 32 keys' fragments
-//   in registers (the next block's requested while the current one is scored), takes
-//   p = exp2(z log2(e)/sqrt(d) - Lambda_r) over 64-row chunks (one chunk's MFMAs beside the
-//   previous chunk's exponentials, also across blocks) and sums it per query head in registers;
-//   the per-head column sums then give the block's pooled and unpooled scores and slice-edge
-//   sums in the layout of the pipelined kernel, so the same selection (with its slice-border
-//   pool repair) follows.
-// Sums run in a fixed order (the only atomics set overflow flags): results are reproducible.
+//   the columns kernel then adds the parts' row sums).  The keys are the A operand, so a lane holds
+//   one window row and sixteen keys, and its row sum and reference are one register each: e =
+//   exp2((z - c_r) log2(e) / sqrt(d)) against a fixed per-row reference c_r = max(logit with the
+//   row's own key, logit with key 0).  The row's log2 normaliser Lambda_r = c_r log2(e)/sqrt(d) +
+//   log2(Z_r) goes to the workspace; a row whose sum overflows (a key more than ~88 natural-log
+//   units above its reference) marks the part, and the columns kernel flags the job for the exact
+//   rescoring of the selection kernels.
+// window_cols_kernel<NRT>: one workgroup per (job, range of 128-key slices).  The window rows are
+//   the A operand, so a lane holds one key and sixteen rows of each block, with their normalisers in
+//   registers; p = exp2(z log2(e)/sqrt(d) - Lambda_r) is summed over a block's rows in registers and
+//   the per-head column sums give the slice's pooled and unpooled scores and slice-edge sums in
+//   the layout of the pipelined kernel, so the same selection (with its slice-border pool repair)
+//   follows.  Jobs, ranges and tiles run in the reverse of the rows kernel's order, so that the keys it
+//   read last are still in the 256 MB last-level cache.
+// Sums run in a fixed order (the only atomic sets a status bit): results are reproducible.
+//
+// Bound: issue of the exponentials and MFMAs (per 64 logits 16 cycles of multiply-add, exponential
+// and addition, beside 16 of the matrix pipe, half of which hold back the VALU too), at the clock the
+// power limit leaves (1.65 GHz).  At 960 jobs of 256 rows and 32768 keys the rows pass takes 1.93 ms
+// (2.38 with 16x16x32 MFMA and 32 rows per wave, 1.09 PFLOP/s now) and the columns pass 2.39 ms
+// (3.04).  Four row tiles are bound by the second reading of the keys: 128 jobs of 20011 keys, 656 MB
+// a pass, 140 and 128 us (150 and 216).
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 
-#include "lds_dma.h"
-#include "rkv_internal.h"
+#include <type_traits>
+
+#include "tile32.h"
 
 namespace rkv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr float kMaskedW = -1e30f;   // exponent of a hidden key: exp2 gives 0
-constexpr int kColBlocks = 32;        // key blocks per columns workgroup
-
-__device__ __forceinline__ bf16x8 as_bf16x8w(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_addw(float x) {
-  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
-}
-
-// LDS position of 16-byte chunk `ch` of row `row` of a [rows][128] bf16 tile (XOR swizzle).
-__device__ __forceinline__ int swzw(int row, int ch) { return (row * 16 + (ch ^ (row & 15))) * 8; }
+constexpr int kPartMark = 2;   // words of a job's counter line from which its parts' overflow marks sit
 
 // Window row r of a job: query head g = r / tpr and window index ii = r % tpr (tpr = rows per
 // head in the padded layout); valid when g < G and ii < w.
@@ -65,16 +61,41 @@ __device__ __forceinline__ WinRow win_row(int r, int tpr, int G, int w) {
   return x;
 }
 
+// Runs `body(buffer, t)` for the tiles t = 0 .. n - 1 (key tile kt0 + kDir t) of the key head, each with
+// its tile in sK[buffer]; the buffer is a compile-time constant.  Tile t + 3 is requested once every
+// wave is past tile t - 1, whose buffer it takes.
+template <int kDir, typename Body>
+__device__ __forceinline__ void stream_keys(const uint16_t* khead, int L, int kt0, int n, uint16_t (*sK)[kTileHalfs],
+                                            int wv, Body&& body) {
+  const uint32_t lds0 = lds_addr(&sK[0][0]);
+#pragma unroll
+  for (int t = 0; t < kRing - 1; ++t)
+    if (t < n) issue_tile(khead, (kt0 + kDir * t) * kTile, L, lds0 + t * (kTileHalfs * 2), wv);
+  auto one = [&](auto buf, int t) __attribute__((always_inline)) {
+    constexpr int b = decltype(buf)::value;
+    wait_tile(n - 1 - t);
+    tile_barrier();
+    if (t + kRing - 1 < n)
+      issue_tile(khead, (kt0 + kDir * (t + kRing - 1)) * kTile, L, lds0 + ((b + kRing - 1) % kRing) * (kTileHalfs * 2), wv);
+    body(buf, t);
+  };
+#pragma unroll 1
+  for (int t = 0; t < n; t += kRing) {
+    one(std::integral_constant<int, 0>{}, t);
+    if (t + 1 < n) one(std::integral_constant<int, 1>{}, t + 1);
+    if (t + 2 < n) one(std::integral_constant<int, 2>{}, t + 2);
+    if (t + 3 < n) one(std::integral_constant<int, 3>{}, t + 3);
+  }
+}
+
 template <int NRT>
-__global__ __launch_bounds__(NRT * 64, 1) void window_rows_kernel(const PrefillLaunch P) {
-  constexpr int R = NRT * 32, NT = NRT * 64;
-  // LDS DMA of a 128-key tile: 32 instructions of 4 keys (1 KiB) each, NI per wave
-  constexpr int NI = kSlice / 4 / NRT;
-  static_assert(NI % 2 == 0 && NRT % 4 == 0, "instruction pairs 4 KiB apart, waves in groups of four");
-  __shared__ __attribute__((aligned(16))) uint16_t sK[2][kSlice * kHeadDim];
+__global__ __launch_bounds__(256, 2) void window_rows_kernel(const PrefillLaunch P) {
+  constexpr int R = NRT * 32, RG = NRT / 2, KG = 4 / RG;   // row groups of 64, key groups of a tile
+  __shared__ __attribute__((aligned(16))) uint16_t sK[kRing][kTileHalfs];
+  __shared__ float sZ[KG][R];
   __shared__ float sC[R];
-  const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, l16 = lane & 15;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wv % RG, kg = wv / RG;
   const int L = P.seq_len, w = P.window, G = P.group, Hq = P.n_q_heads, Hkv = P.n_kv_heads, B = P.batch;
   const int tpr = P.row_tiles_per_group * 32;
   const int parts = P.window_parts, job = blockIdx.x / parts, part = blockIdx.x - job * parts;
@@ -82,220 +103,121 @@ __global__ __launch_bounds__(NRT * 64, 1) void window_rows_kernel(const PrefillL
   const PrefillLayer& ly = P.layer[slot];
   const uint16_t* khead = ly.k + (size_t)(s * Hkv + h) * L * kHeadDim;
   const uint16_t* qjob = ly.q + (size_t)(s * Hq + h * G) * w * kHeadDim;   // [G][w][d]
-  // this workgroup's key tiles [t0, t1) (part `part` of the job's tiles)
-  const int n_tiles = (L + kSlice - 1) / kSlice;
-  const int per_part = (n_tiles + parts - 1) / parts;
-  const int t0 = min(n_tiles, part * per_part), t1 = min(n_tiles, t0 + per_part);
+  // this workgroup's key tiles [t0, t0 + n) (part `part` of the job's tiles)
+  const int n_tiles = (L + kTile - 1) / kTile, per_part = (n_tiles + parts - 1) / parts;
+  const int t0 = min(n_tiles, part * per_part), n = min(n_tiles, t0 + per_part) - t0;
 
-  // ---- per-row reference (every part computes the same): thread r < R takes row r (its own key and key 0, 128-d dot products)
+  // the wave's rows 64 rg + 32 b + l32, their references and last visible keys
+  bf16x8 q[2][8];
+  float ncs[2], Z[2] = {0.f, 0.f};
+  int last[2];
+  const float sl2 = P.scale_log2;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const WinRow x = win_row(64 * rg + 32 * b + l32, tpr, G, w);
+    load_block(x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr, q[b]);
+    last[b] = x.valid ? L - w + x.ii : L - 1;
+    const float c = fmaxf(block_dot(q[b], khead + (size_t)last[b] * kHeadDim), block_dot(q[b], khead));
+    if (kg == 0 && hf == 0) sC[64 * rg + 32 * b + l32] = c;
+    ncs[b] = -c * sl2;
+  }
+  f32x16 accA[2], accB[2];
+  hide_all(accB);
+  const uint32_t tl = tile_lane();
+  // a subtile's exponentials are summed by themselves first: the row sums then take an addition per
+  // subtile, and the rounding of many small terms added to a large one stays out of them
+  float zs[2][2];
+  auto exps = [&](const f32x16 (&v)[2], int u) __attribute__((always_inline)) {
+    const int b = u >> 4, i = u & 15;
+    const float e = __builtin_amdgcn_exp2f(fmaf(v[b][i], sl2, ncs[b]));
+    if (i < 2) zs[b][i] = e;
+    else zs[b][i & 1] += e;
+  };
+  // a subtile of keys k0 .. k0 + 31, with the exponentials of the one before it
+  auto step = [&](const uint16_t* tile, int sub, int k0, f32x16 (&cur)[2], const f32x16 (&prev)[2]) __attribute__((always_inline)) {
+    tile_step<true>(tile, tl, sub, q, cur, [&](int u) __attribute__((always_inline)) { exps(prev, u); });
+#pragma unroll
+    for (int b = 0; b < 2; ++b) Z[b] += zs[b][0] + zs[b][1];
+    keep_here(Z);
+    if (k0 + 31 > L - w) {   // keys past a row's position (or the prompt) take no part
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (k0 + acc_row(i) + 4 * hf > last[b]) cur[b][i] = kHidden;
+    }
+  };
+  stream_keys<1>(khead, L, t0, n, sK, wv, [&](auto buf, int t) __attribute__((always_inline)) {
+    constexpr int b = decltype(buf)::value;
+    const int k0 = (t0 + t) * kTile;
+    if constexpr (KG == 1) {
+      step(sK[b], 0, k0, accA, accB);
+      step(sK[b], 1, k0 + 32, accB, accA);
+    } else if constexpr ((b & 1) == 0) {
+      step(sK[b], kg, k0 + 32 * kg, accA, accB);
+    } else {
+      step(sK[b], kg, k0 + 32 * kg, accB, accA);
+    }
+  });
+  if (KG == 1 || (n & 1) == 0) {
+#pragma unroll
+    for (int u = 0; u < 32; ++u) exps(accB, u);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 32; ++u) exps(accA, u);
+  }
+  // sums over the lane halves and the key groups; the row's log2 normaliser (one part), or the part's
+  // row sum and, from part 0, the reference (several parts: the columns kernel adds them)
+#pragma unroll
+  for (int b = 0; b < 2; ++b) Z[b] += zs[b][0] + zs[b][1];
+  {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(Z[0]), __float_as_uint(Z[1]), false, false);
+    sZ[kg][64 * rg + lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane half hf has block hf
+  }
+  tile_barrier();
+  bool over = false;
   if (tid < R) {
     const WinRow x = win_row(tid, tpr, G, w);
-    float zd = 0.f, zs = 0.f;
-    if (x.valid) {
-      const u32x4* qp = reinterpret_cast<const u32x4*>(qjob + (size_t)(x.g * w + x.ii) * kHeadDim);
-      const u32x4* kd = reinterpret_cast<const u32x4*>(khead + (size_t)(L - w + x.ii) * kHeadDim);
-      const u32x4* ks = reinterpret_cast<const u32x4*>(khead);
+    float z = sZ[0][tid];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const u32x4 qa = qp[c], da = kd[c], sa = ks[c];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float q0 = __uint_as_float(qa[u] << 16), q1 = __uint_as_float(qa[u] & 0xffff0000u);
-          zd = fmaf(q0, __uint_as_float(da[u] << 16), zd);
-          zd = fmaf(q1, __uint_as_float(da[u] & 0xffff0000u), zd);
-          zs = fmaf(q0, __uint_as_float(sa[u] << 16), zs);
-          zs = fmaf(q1, __uint_as_float(sa[u] & 0xffff0000u), zs);
-        }
-      }
-    }
-    sC[tid] = fmaxf(zd, zs);
-  }
-  // ---- the wave's query fragments: rows 32 wv + 16 rs + l16, chunk 4 st + lg
-  bf16x8 qa[2][4];
-#pragma unroll
-  for (int rs = 0; rs < 2; ++rs) {
-    const WinRow x = win_row(32 * wv + 16 * rs + l16, tpr, G, w);
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (x.valid) v = *reinterpret_cast<const u32x4*>(qjob + (size_t)(x.g * w + x.ii) * kHeadDim + 8 * (4 * st + lg));
-      qa[rs][st] = as_bf16x8w(v);
-    }
-  }
-  // Wave wv moves instructions I = (wv % 4) + 4 u + 16 (wv / 4), u = 0 .. NI - 1: keys 4 I + [0, 4)
-  // of the tile, lane l filling key 4 I + l / 16 at chunk position l % 16 (the XOR swizzle of
-  // swzw, so the lane's source chunk is (l % 16) ^ ((4 I + l / 16) % 16)).  I % 4 is the wave's,
-  // so the lane's byte offset is the same for every instruction; instructions u and u + 1 are
-  // 4 KiB apart and go as one pair.  The tile past the prompt's end repeats its last key.
-  const uint32_t dma_off = (uint32_t)(lane >> 4) * 256u + (uint32_t)((lane & 15) ^ (4 * (wv & 3) + (lane >> 4))) * 16u;
-  const int i0 = (wv & 3) + 16 * (wv >> 2);
-  auto issue = [&](int kt, int buf) {
-    const uint32_t lds0 = lds_addr(&sK[buf][0]);
-    if (kt * kSlice + kSlice <= L) {
-      const char* tile = reinterpret_cast<const char*>(khead + (size_t)kt * kSlice * kHeadDim);
-#pragma unroll
-      for (int u = 0; u < NI; u += 2) {
-        const int I = i0 + 4 * u;
-        dma16s_pair(tile + 1024u * I, dma_off, lds0 + 1024u * I);
-      }
+    for (int k = 1; k < KG; ++k) z += sZ[k][tid];
+    over = x.valid && !(z < __builtin_inff());   // a key far above the row's reference
+    const float c = sC[tid] * sl2;
+    if (parts == 1) {
+      // padding and overflowing rows: +inf, every probability 0
+      P.lam[(size_t)job * R + tid] = x.valid && z < __builtin_inff() ? add_log2(c, z) : __builtin_inff();
     } else {
-#pragma unroll
-      for (int u = 0; u < NI; ++u) {
-        const int I = i0 + 4 * u, r = 4 * I + (lane >> 4);
-        const int key = min(kt * kSlice + r, L - 1);
-        dma16(khead + (size_t)key * kHeadDim + 8 * ((lane & 15) ^ (r & 15)), lds0 + 1024u * I);
-      }
+      P.stats[((size_t)job * parts + part) * R + tid] = z;
+      if (part == 0) P.ncl[(size_t)job * R + tid] = x.valid ? c : __builtin_inff();
     }
-  };
-  // the first two tiles (the second stays in flight)
-  if (t0 < t1) issue(t0, 0);
-  if (t0 + 1 < t1) issue(t0 + 1, 1);
-  __syncthreads();   // sC complete
-  const float sl2 = P.scale_log2;
-  float ncs[2][4], Z[2][4];
-  int last[2][4];   // the row's last visible key (-1: a padding row)
-#pragma unroll
-  for (int rs = 0; rs < 2; ++rs)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 32 * wv + 16 * rs + 4 * lg + i;
-      const WinRow x = win_row(r, tpr, G, w);
-      ncs[rs][i] = -sC[r] * sl2;
-      Z[rs][i] = 0.f;
-      last[rs][i] = x.valid ? L - w + x.ii : -1;
-    }
-  // logits of key sub-tiles ks0 .. ks0 + 3 (16 keys each) of the tile in buffer buf
-  auto mfma_half = [&](int buf, int ks0, f32x4 (&a)[2][4]) {
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&sK[buf][swzw(16 * (ks0 + ks) + l16, 4 * st + lg)]);
-        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        a[0][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[0][st], kf, st == 0 ? z : a[0][ks], 0, 0, 0);
-        a[1][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[1][st], kf, st == 0 ? z : a[1][ks], 0, 0, 0);
-      }
-  };
-  auto valu_half = [&](const f32x4 (&a)[2][4]) {
-#pragma unroll
-    for (int rs = 0; rs < 2; ++rs)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) Z[rs][i] += __builtin_amdgcn_exp2f(fmaf(a[rs][ks][i], sl2, ncs[rs][i]));
-  };
-  // one MFMA half interleaved with the exponentials of the other (step j reads fragment j + 2,
-  // runs the two MFMAs of fragment j and two logits' exponentials; a scheduling barrier closes
-  // the step); the order of the sums is that of valu_half
-  auto interleaved = [&](int buf, int ks0, f32x4 (&a)[2][4], const f32x4 (&v)[2][4]) {
-    auto frag = [&](int j) {
-      return *reinterpret_cast<const bf16x8*>(&sK[buf][swzw(16 * (ks0 + (j & 3)) + l16, 4 * (j >> 2) + lg)]);
-    };
-    bf16x8 f[3];
-    f[0] = frag(0);
-    f[1] = frag(1);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (j + 2 < 16) f[(j + 2) % 3] = frag(j + 2);
-      const int st = j >> 2, ks = j & 3;
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      a[0][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[0][st], f[j % 3], st == 0 ? z : a[0][ks], 0, 0, 0);
-      a[1][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[1][st], f[j % 3], st == 0 ? z : a[1][ks], 0, 0, 0);
-#pragma unroll
-      for (int uu = 0; uu < 2; ++uu) {
-        const int u = 2 * j + uu, rs = u >> 4, kv = (u >> 2) & 3, i = u & 3;
-        Z[rs][i] += __builtin_amdgcn_exp2f(fmaf(v[rs][kv][i], sl2, ncs[rs][i]));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  f32x4 accA[2][4], accB[2][4];
-  // bulk tiles: every key visible to every window row (keys below L - w + 1, the first row's
-  // position, all inside the prompt); buffer parity counts from t0
-  const int b_end = min(t1, (L - w + 1) / kSlice);
-  // tile t0 in (this wave's part; then every wave's)
-  if (t0 + 1 < t1) wait_vmcnt<NI>();
-  else wait_vmcnt<0>();
-  __syncthreads();
-  if (t0 < b_end) mfma_half(0, 0, accA);
-  for (int kt = t0; kt < b_end; ++kt) {
-    const int b = (kt - t0) & 1;
-    interleaved(b, 4, accB, accA);
-    // tile kt + 1 (issued an iteration ago) in; after the barrier every wave is done with
-    // buffer b, which takes tile kt + 2
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (kt + 2 < t1) issue(kt + 2, b);
-    if (kt + 1 < b_end) interleaved(b ^ 1, 0, accA, accB);
-    else valu_half(accB);
   }
-  // edge tiles: keys past a row's position, and past the prompt, take no part
-  for (int kt = max(t0, b_end); kt < t1; ++kt) {
-    const int k0 = kt * kSlice, b = (kt - t0) & 1;
-    mfma_half(b, 0, accA);
-    mfma_half(b, 4, accB);
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-      for (int rs = 0; rs < 2; ++rs)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float x = fmaf(hf == 0 ? accA[rs][ks][i] : accB[rs][ks][i], sl2, ncs[rs][i]);
-            const int key = k0 + 16 * (4 * hf + ks) + l16;
-            if (key > last[rs][i]) x = kMaskedW;
-            Z[rs][i] += __builtin_amdgcn_exp2f(x);
-          }
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (kt + 2 < t1) issue(kt + 2, b);
+  // The part's overflow mark, for the columns kernel; it also starts the call's status word.
+  const int any = __syncthreads_or(over);
+  if (tid == 0) {
+    P.counters[(size_t)kCounterStride * (1 + job) + kPartMark + part] = any ? 1u : 0u;
+    if (blockIdx.x == 0 && P.first_group) P.counters[0] = 0u;
   }
-  // ---- sums over the 16 lanes of each row group; the row's log2 normaliser (one part), or the
-  // part's row sum and, from part 0, the reference (several parts: the columns kernel adds them)
-#pragma unroll
-  for (int rs = 0; rs < 2; ++rs)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float z = Z[rs][i];
-      z = dpp_addw<0x128>(z);
-      z = dpp_addw<0x124>(z);
-      z = dpp_addw<0x122>(z);
-      z = dpp_addw<0x121>(z);
-      const int r = 32 * wv + 16 * rs + 4 * lg + i;
-      if (l16 == 0) {
-        const bool valid = last[rs][i] >= 0;
-        if (valid && !(z < __builtin_inff())) {
-          // a key far above the row's reference: the job is rescored exactly before selection
-          atomicOr(P.counters, RKV_STATUS_REPAIRED);
-          atomicOr(P.counters + (size_t)kCounterStride * (1 + job) + 1, 1u);
-        }
-        if (parts == 1) {
-          // padding and overflowing rows: +inf, every probability 0
-          P.lam[(size_t)job * R + r] = valid && z < __builtin_inff() ? sC[r] * sl2 + __builtin_log2f(z)
-                                                                      : __builtin_inff();
-        } else {
-          P.stats[((size_t)job * parts + part) * R + r] = z;
-          if (part == 0) P.ncl[(size_t)job * R + r] = valid ? sC[r] * sl2 : __builtin_inff();
-        }
-      }
-    }
 }
 
 template <int NRT>
 __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch P) {
-  constexpr int R = NRT * 32, NT = 256, NCH = NRT / 2;   // NCH chunks of 64 rows (two row tiles)
-  constexpr int PERQ = R * kHeadDim / 8 / NT;            // 16-byte query chunks per thread
-  static_assert(NCH % 2 == 0, "chunks alternate between two accumulator sets");
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[R * kHeadDim];
+  constexpr int R = NRT * 32, NT = 256, RG = NRT / 2, KG = 4 / RG;
+  __shared__ __attribute__((aligned(16))) uint16_t sK[kRing][kTileHalfs];
+  // column sums of a slice's keys, per 32-row block (an odd number of row tiles per head) or per
+  // 64-row pair of blocks (an even number: both belong to one head); two slices in flight
+  constexpr int kPad = 4, kColRow = kSlice + 2 * kPad;   // rows with a zero margin at both ends
+  __shared__ float sCol[2][NRT][kColRow];
   __shared__ __attribute__((aligned(16))) float sLam[R];
-  __shared__ float sColH[2][kMaxRowTiles][kSlice];   // per query head: column sums of a block's keys
-  const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, l16 = lane & 15;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wv % RG, kg = wv / RG;
   const int L = P.seq_len, w = P.window, G = P.group, Hq = P.n_q_heads, Hkv = P.n_kv_heads, B = P.batch;
-  const int nsl = P.n_slices, tpr = P.row_tiles_per_group * 32, NTH = P.row_tiles_per_group;
-  const int nbg = (nsl + kColBlocks - 1) / kColBlocks;
-  const int job = blockIdx.x / nbg, bg = blockIdx.x - job * nbg;
+  const int nsl = P.n_slices, NTH = P.row_tiles_per_group, tpr = NTH * 32;
+  const bool pair = NTH % 2 == 0;
+  const int per_head = pair ? NTH / 2 : NTH;   // sCol rows of a head
+  const int ranges = P.window_ranges, per_range = (nsl + ranges - 1) / ranges;
+  const int block = gridDim.x - 1 - blockIdx.x;   // what the rows kernel read last comes first
+  const int job = block / ranges, range = block - job * ranges;
+  const int b0 = min(nsl, range * per_range), b1 = min(nsl, b0 + per_range), n = 2 * (b1 - b0);
   const int h = job % Hkv, s = (job / Hkv) % B, slot = job / (Hkv * B);
   const PrefillLayer& ly = P.layer[slot];
   const bool snap = ly.rule == RKV_SNAPKV;
@@ -303,166 +225,130 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
   const uint16_t* qjob = ly.q + (size_t)(s * Hq + h * G) * w * kHeadDim;
   const float sl2 = P.scale_log2, inv_g = 1.f / (float)G;
   const int npre = L - w, ph = P.pool_half;
+  if (range == 0 && tid == 0) {
+    // a job with an overflowing row is rescored exactly before selection
+    uint32_t* line = P.counters + (size_t)kCounterStride * (1 + job);
+    uint32_t any = 0u;
+    for (int p = 0; p < P.window_parts; ++p) any |= line[kPartMark + p];
+    line[1] = any;
+    if (any) atomicOr(P.counters, RKV_STATUS_REPAIRED);
+  }
+  if (n <= 0) return;
 
-  // ---- the job's query block (padding rows zero) and row normalisers into LDS
-#pragma unroll
-  for (int u = 0; u < PERQ; ++u) {
-    const int c = tid + NT * u, row = c >> 4, ch = c & 15;
-    const WinRow x = win_row(row, tpr, G, w);
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (x.valid) v = *reinterpret_cast<const u32x4*>(qjob + (size_t)(x.g * w + x.ii) * kHeadDim + 8 * ch);
-    *reinterpret_cast<u32x4*>(&sQ[swzw(row, ch)]) = v;
+  if (tid < 2 * NRT * 2 * kPad) {
+    const int o = tid % (2 * kPad);
+    (&sCol[0][0][0])[tid / (2 * kPad) * kColRow + (o < kPad ? o : kSlice + o)] = 0.f;
   }
   if (P.window_parts == 1) {
-    for (int r = tid; r < R; r += NT) sLam[r] = P.lam[(size_t)job * R + r];
-  } else {
+    if (tid < R) sLam[tid] = P.lam[(size_t)job * R + tid];
+  } else if (tid < R) {
     // the parts' row sums, added in part order; +inf for padding and overflowing rows
     const int parts = P.window_parts;
-    for (int r = tid; r < R; r += NT) {
-      const float c = P.ncl[(size_t)job * R + r];
-      float z = 0.f;
-      for (int q = 0; q < parts; ++q) z += P.stats[((size_t)job * parts + q) * R + r];
-      sLam[r] = c < __builtin_inff() && z < __builtin_inff() ? c + __builtin_log2f(z) : __builtin_inff();
-    }
+    const float c = P.ncl[(size_t)job * R + tid];
+    float z = 0.f;
+    for (int p = 0; p < parts; ++p) z += P.stats[((size_t)job * parts + p) * R + tid];
+    sLam[tid] = c < __builtin_inff() && z < __builtin_inff() ? add_log2(c, z) : __builtin_inff();
   }
-  // ---- this wave's 32 keys of block b as B-operand fragments (key 32 wv + 16 ks + l16)
-  auto load_k = [&](int b, bf16x8 (&kf)[2][4]) {
+  bf16x8 q[2][8];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int key = min(b * kSlice + 32 * wv + 16 * ks + l16, L - 1);
+  for (int b = 0; b < 2; ++b) {
+    const WinRow x = win_row(64 * rg + 32 * b + l32, tpr, G, w);
+    load_block(x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr, q[b]);
+  }
+  tile_barrier();
+  // minus the normalisers of the rows this lane's accumulators hold
+  f32x4 nl[2][4];
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
-        kf[ks][st] = as_bf16x8w(*reinterpret_cast<const u32x4*>(khead + (size_t)key * kHeadDim + 8 * (4 * st + lg)));
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      nl[b][u] = *reinterpret_cast<const f32x4*>(&sLam[64 * rg + 32 * b + 8 * u + 4 * hf]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nl[b][u][i] = -nl[b][u][i];
+    }
+  float cs[2][2];
+  auto exps = [&](const f32x16 (&v)[2], int u) __attribute__((always_inline)) {
+    const int b = u >> 4, i = u & 15;
+    const float e = __builtin_amdgcn_exp2f(fmaf(v[b][i], sl2, nl[b][i >> 2][i & 3]));
+    if (i < 2) cs[b][i] = e;
+    else cs[b][i & 1] += e;
+  };
+  // the column sums of a subtile: key offset kb of the slice in buffer sb (both constants)
+  auto put = [&](int sb, int kb) __attribute__((always_inline)) {
+    const float c0 = cs[0][0] + cs[0][1], c1 = cs[1][0] + cs[1][1];
+    if (pair) {
+      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0 + c1), __float_as_uint(c0 + c1), false, false);
+      if (hf == 0) sCol[sb][rg][kPad + kb + l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    } else {
+      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0), __float_as_uint(c1), false, false);
+      sCol[sb][2 * rg + hf][kPad + kb + l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane half hf: block hf
     }
   };
-  const int b0 = bg * kColBlocks, b1 = min(nsl, b0 + kColBlocks);
-  bf16x8 kcur[2][4], knext[2][4];
-  load_k(b0, kcur);
-  __syncthreads();
-
-  // Q fragment j = 4 st + rs of chunk c: rows 64 c + 16 rs + l16, 16-byte chunk 4 st + lg
-  auto qfrag = [&](int c, int j) {
-    return *reinterpret_cast<const bf16x8*>(&sQ[swzw(64 * c + 16 * (j & 3) + l16, 4 * (j >> 2) + lg)]);
-  };
-  // logits of chunk c: a[rs][ks][i] = row 64 c + 16 rs + 4 lg + i, key 32 wv + 16 ks + l16
-  auto mfma_chunk = [&](int c, const bf16x8 (&kf)[2][4], f32x4 (&a)[4][2]) {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int st = j >> 2, rs = j & 3;
-      const bf16x8 qf = qfrag(c, j);
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      a[rs][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf, kf[0][st], st == 0 ? z : a[rs][0], 0, 0, 0);
-      a[rs][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf, kf[1][st], st == 0 ? z : a[rs][1], 0, 0, 0);
-    }
-  };
-  auto lam_chunk = [&](int c, f32x4 (&lm)[4]) {
-#pragma unroll
-    for (int rs = 0; rs < 4; ++rs) lm[rs] = *reinterpret_cast<const f32x4*>(&sLam[64 * c + 16 * rs + 4 * lg]);
-  };
-  // probabilities of a chunk's logits summed per lane into ct[row tile][ks]; value u of the 32 a
-  // lane holds is (rs, ks, i) = (u / 8, (u / 4) % 2, u % 4)
-  auto exps_plain = [&](const f32x4 (&a)[4][2], const f32x4 (&lm)[4], float (&ct)[2][2]) {
-#pragma unroll
-    for (int u = 0; u < 32; ++u) {
-      const int rs = u >> 3, ks = (u >> 2) & 1, i = u & 3;
-      ct[rs >> 1][ks] += __builtin_amdgcn_exp2f(fmaf(a[rs][ks][i], sl2, -lm[rs][i]));
-    }
-  };
-  // blocks with keys past a row's position (or past the prompt): those keys and padding rows
-  // take no part
-  auto exps_masked = [&](int c, int kbase, const f32x4 (&a)[4][2], const f32x4 (&lm)[4], float (&ct)[2][2]) {
-#pragma unroll
-    for (int u = 0; u < 32; ++u) {
-      const int rs = u >> 3, ks = (u >> 2) & 1, i = u & 3;
-      float x = fmaf(a[rs][ks][i], sl2, -lm[rs][i]);
-      const WinRow y = win_row(64 * c + 16 * rs + 4 * lg + i, tpr, G, w);
-      if (!y.valid || kbase + 16 * ks + l16 > L - w + y.ii) x = kMaskedW;
-      ct[rs >> 1][ks] += __builtin_amdgcn_exp2f(x);
-    }
-  };
-  // the MFMAs of chunk cn against keys kf (into a) interleaved with the exponentials of the
-  // previous chunk's logits v, in the order of exps_plain: step j reads Q fragment j + 2, runs
-  // fragment j's two MFMAs and two exponentials; a scheduling barrier closes the step
-  auto interleaved = [&](int cn, const bf16x8 (&kf)[2][4], f32x4 (&a)[4][2], const f32x4 (&v)[4][2],
-                         const f32x4 (&lm)[4], float (&ct)[2][2]) {
-    bf16x8 f[3];
-    f[0] = qfrag(cn, 0);
-    f[1] = qfrag(cn, 1);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (j + 2 < 16) f[(j + 2) % 3] = qfrag(cn, j + 2);
-      const int st = j >> 2, rs = j & 3;
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      a[rs][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j % 3], kf[0][st], st == 0 ? z : a[rs][0], 0, 0, 0);
-      a[rs][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j % 3], kf[1][st], st == 0 ? z : a[rs][1], 0, 0, 0);
-#pragma unroll
-      for (int uu = 0; uu < 2; ++uu) {
-        const int u = 2 * j + uu, rv = u >> 3, ks = (u >> 2) & 1, i = u & 3;
-        ct[rv >> 1][ks] += __builtin_amdgcn_exp2f(fmaf(v[rv][ks][i], sl2, -lm[rv][i]));
+  // Scores of slice b from the column sums in buffer sb.  The common forms (one sCol row per head, no
+  // mask border in the slice, a 7-wide pool where pooled) take one wave pair for the keys, every head
+  // of a key in one thread, and the other pair for the slice-edge sums.  Their pool windows are cut by
+  // the zero margins of sCol instead of clamped indices: the sums are non-negative, so a margin never
+  // is the maximum, and the maximum of the bit patterns is the maximum of the values.
+  auto store = [&](int b, int sb) __attribute__((always_inline)) {
+    int tid = threadIdx.x;   // opaque: no per-thread address is kept across the loop
+    asm volatile("" : "+v"(tid));
+    const float(*col)[kColRow] = sCol[sb];
+    const int cbase = b * kSlice;
+    float* Srow = P.S + (size_t)job * L + cbase;
+    if (per_head == 1 && cbase + kSlice <= npre && (!snap || ph == 3)) {
+      const int t2 = tid ^ (sb << 7);   // the wave pairs take turns
+      if (t2 < kSlice) {
+        const float* c = &col[0][kPad + t2];
+        float su = 0.f, sc = 0.f;
+        if (snap) {
+#pragma unroll 4
+          for (int g = 0; g < G; ++g, c += kColRow) {
+            const uint32_t* u = reinterpret_cast<const uint32_t*>(c);
+            const uint32_t m = max(max(max(u[-3], u[-2]), max(u[-1], u[0])), max(max(u[1], u[2]), u[3]));
+            su += c[0];
+            sc += __uint_as_float(m);
+          }
+          Srow[t2] = sc * inv_g;
+          if (P.want_unpooled) P.Su[(size_t)job * L + cbase + t2] = su * inv_g;
+        } else {
+#pragma unroll 4
+          for (int g = 0; g < G; ++g, c += kColRow) su += c[0];
+          Srow[t2] = su * inv_g;
+        }
+      } else if (snap && t2 - kSlice < 12 * G) {   // offsets 0 .. 5 and 122 .. 127 of every head
+        const int e = t2 - kSlice, g = e / 12, o = e - 12 * g;
+        P.edge[((size_t)job * nsl + b) * G * 12 + e] = col[g][kPad + (o < 6 ? o : kSlice - 12 + o)];
       }
-      __builtin_amdgcn_sched_barrier(0);
+      return;
     }
-  };
-  // sums over the wave's four row groups (lanes l, l ^ 32, then l ^ 16), then per query head:
-  // row tile t = 2 c + tt belongs to head t / NTH; a head's sum runs over its tiles in order and
-  // goes to sColH when its last tile is in (lanes 0-31: key 32 wv + 16 lg + l16)
-  auto heads = [&](int c, int buf, float (&ct)[2][2], float (&hs)[2]) {
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const auto p0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(ct[tt][ks]), __float_as_uint(ct[tt][ks]), false, false);
-        const float v = __uint_as_float(p0[0]) + __uint_as_float(p0[1]);
-        const auto p1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        ct[tt][ks] = __uint_as_float(p1[0]) + __uint_as_float(p1[1]);
-      }
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int t = 2 * c + tt;
-      hs[0] += ct[tt][0];
-      hs[1] += ct[tt][1];
-      if ((t + 1) % NTH == 0) {
-        const int g = t / NTH;
-        if (g < G && lane < 32) sColH[buf][g][32 * wv + 16 * lg + l16] = lg == 0 ? hs[0] : hs[1];
-        hs[0] = hs[1] = 0.f;
-      }
-    }
-  };
-  // scores of block b from the per-head column sums; thread = (key, query-head half)
-  auto store = [&](int b, int buf) {
-    const int cbase = b * kSlice, kl = tid >> 1, kk = cbase + kl;
+    auto head = [&](int g, int kl) {
+      float v = col[g * per_head][kPad + kl];
+      for (int u = 1; u < per_head; ++u) v += col[g * per_head + u][kPad + kl];
+      return v;
+    };
+    // thread = (key, query-head half)
+    const int kl = tid >> 1, kk = cbase + kl;
     const int g0 = (tid & 1) * ((G + 1) >> 1), g1 = min(G, g0 + ((G + 1) >> 1));
-    const float NEG_INF = -__builtin_inff();
     float su = 0.f, sc = 0.f;
     if (kk < L) {
-      // max-pool window [lo, hi] inside the block and the prefix [0, L - w); clamping a
-      // neighbour into it repeats a member, so the reads need no branches (for window keys the
-      // pooled value is not used)
+      // max-pool window [lo, hi] inside the slice and the prefix [0, L - w); clamping a
+      // neighbour into it repeats a member (for window keys the pooled value is not used)
       const int lo = max(kk - ph, cbase) - cbase;
       const int hi = max(min(min(kk + ph, cbase + kSlice - 1), npre - 1) - cbase, lo);
       for (int g = g0; g < g1; ++g) {
-        const float* cg = sColH[buf][g];
-        su += cg[kl];
+        su += head(g, kl);
         if (snap) {
-          float m = NEG_INF;
-          if (ph == 3) {
-            float x[7];
-#pragma unroll
-            for (int u = 0; u < 7; ++u) x[u] = cg[min(max(kl - 3 + u, lo), hi)];
-#pragma unroll
-            for (int u = 0; u < 7; ++u) m = fmaxf(m, x[u]);
-          } else {
-            for (int u = 0; u <= 2 * ph; ++u) m = fmaxf(m, cg[min(max(kl - ph + u, lo), hi)]);
-          }
+          float m = 0.f;
+          for (int u = 0; u <= 2 * ph; ++u) m = fmaxf(m, head(g, min(max(kl - ph + u, lo), hi)));
           sc += m;
         }
       }
     }
-    su += __shfl_xor(su, 1);
-    sc += __shfl_xor(sc, 1);
+    su += dpp_pair(su);   // the other head half's sum (lane ^ 1)
+    sc += dpp_pair(sc);
     if ((tid & 1) == 0 && kk < L) {
       su *= inv_g;
-      P.S[(size_t)job * L + kk] = snap && kk < npre ? sc * inv_g : su;
+      Srow[kl] = snap && kk < npre ? sc * inv_g : su;
       if (snap && P.want_unpooled) P.Su[(size_t)job * L + kk] = su;
     }
     if (snap && ph > 0) {   // slice-edge column sums per head: offsets [0, 2 ph) and [128 - 2 ph, 128)
@@ -471,66 +357,55 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
       for (int e2 = tid; e2 < G * E; e2 += NT) {
         const int g = e2 / E, o = e2 - g * E;
         const int kl2 = o < twoP ? o : kSlice - twoP + (o - twoP);
-        ed[e2] = (cbase + kl2 < L) ? sColH[buf][g][kl2] : 0.f;
+        ed[e2] = (cbase + kl2 < L) ? head(g, kl2) : 0.f;
       }
     }
   };
-
-  // The pipeline runs across blocks: the MFMAs of a block's first chunk go beside the previous
-  // block's last exponentials when both blocks are free of masks for this wave (chained).
-  int buf = 0;
-  bool chained = false;   // accA holds chunk 0 of block b
-  f32x4 accA[4][2], accB[4][2];
-  for (int b = b0; b < b1; ++b, buf ^= 1) {
-    if (b + 1 < b1) load_k(b + 1, knext);
-    const int kbase = b * kSlice + 32 * wv;
-    float hs[2] = {0.f, 0.f};
-    f32x4 lm[4];
-    if (kbase + 31 <= L - w) {
-      // every key of the wave visible to every window row: chunk c + 1's MFMAs run beside chunk
-      // c's exponentials
-      const bool chain_next = b + 1 < b1 && kbase + kSlice + 31 <= L - w;
-      if (!chained) mfma_chunk(0, kcur, accA);
+  const uint32_t tl = tile_lane();
+  f32x16 accA[2], accB[2];
+  hide_all(accB);
+  // the subtile at key ka, beside the exponentials of the one before it, whose sums then go to (sb, kb)
+  auto step = [&](const uint16_t* tile, int sub, int ka, int sb, int kb, f32x16 (&cur)[2], const f32x16 (&prev)[2])
+                  __attribute__((always_inline)) {
+    tile_step<false>(tile, tl, sub, q, cur, [&](int u) __attribute__((always_inline)) { exps(prev, u); });
+    put(sb, kb);
+    if (ka + 31 > L - w) {   // keys past a row's position (or the prompt) take no part
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        float ct[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
-        lam_chunk(c, lm);
-        if (c + 1 < NCH) {
-          if ((c & 1) == 0) interleaved(c + 1, kcur, accB, accA, lm, ct);
-          else interleaved(c + 1, kcur, accA, accB, lm, ct);
-        } else if (chain_next) {
-          interleaved(0, knext, accA, accB, lm, ct);   // NCH is even: the last chunk is in accB
-        } else {
-          exps_plain(accB, lm, ct);
-        }
-        heads(c, buf, ct, hs);
-      }
-      chained = chain_next;
-    } else {
-#pragma unroll 1
-      for (int c = 0; c < NCH; ++c) {
-        float ct[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
-        mfma_chunk(c, kcur, accA);
-        lam_chunk(c, lm);
-        exps_masked(c, kbase, accA, lm, ct);
-        heads(c, buf, ct, hs);
-      }
-      chained = false;
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)   // window index of the block's first row, plus the row in the block
+          if (ka + l32 > L - w + 32 * ((2 * rg + b) % NTH) + acc_row(i) + 4 * hf) cur[b][i] = kHidden;
     }
-    __syncthreads();   // sColH[buf] complete; the buffer is written again two blocks later
-    store(b, buf);
+  };
+  // Tiles and slices run downwards.  The slice of tile t is in column buffer (t / 2) % 2.  Its last sums are written during the next
+  // slice's first tile, so its scores are stored in that slice's second tile, after the barrier; the
+  // buffer is written again from the first tile of the slice after that.  (The first step of all puts
+  // zeros where the second slice comes.)
+  stream_keys<-1>(khead, L, 2 * b1 - 1, n, sK, wv, [&](auto buf, int t) __attribute__((always_inline)) {
+    constexpr int b = decltype(buf)::value, pb = (b + kRing - 1) % kRing;   // this tile's buffer, the one before
+    const int ka = (2 * b1 - 1 - t) * kTile;
+    if constexpr (KG == 1) {
+      step(sK[b], 0, ka, pb / 2, b % 2 * kTile + 32, accA, accB);
+      step(sK[b], 1, ka + 32, b / 2, pb % 2 * kTile, accB, accA);
+    } else if constexpr (b % 2 == 0) {
+      step(sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg, accA, accB);
+    } else {
+      step(sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg, accB, accA);
+    }
+    if (b % 2 == 1 && t >= 3) store(b1 - t / 2, 1 - b / 2);
+  });
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int st = 0; st < 4; ++st) kcur[ks][st] = knext[ks][st];
-  }
+  for (int u = 0; u < 32; ++u) exps(accB, u);   // n is even: the last subtile's
+  const int sb = (b1 - 1 - b0) & 1;
+  put(sb, KG == 1 ? 32 : 32 * kg);
+  tile_barrier();
+  store(b0, sb);
 }
 
 template <int NRT>
 int launch_window_nrt(const PrefillLaunch& P, int n_jobs, hipStream_t st) {
-  window_rows_kernel<NRT><<<n_jobs * P.window_parts, NRT * 64, 0, st>>>(P);
-  const int nbg = (P.n_slices + kColBlocks - 1) / kColBlocks;
-  window_cols_kernel<NRT><<<(unsigned)((int64_t)n_jobs * nbg), 256, 0, st>>>(P);
+  window_rows_kernel<NRT><<<n_jobs * P.window_parts, 256, 0, st>>>(P);
+  window_cols_kernel<NRT><<<(unsigned)((int64_t)n_jobs * P.window_ranges), 256, 0, st>>>(P);
   return (int)hipGetLastError();
 }
 

@@ -1,0 +1,35 @@
+"""GPU parity of the window scoring kernels at the edges of their tiles: 64-key tiles in a ring of
+four, 32-key subtiles, 128-key slices, four and eight row tiles, one to four row tiles per head,
+padded rows, split keys.  Against the oracle, at the bar of the other prefill tests."""
+import pytest
+
+from oracle import prefill as OP
+from test_gpu_prefill import gen, run_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # L, w, Hq, Hkv, pool
+    (64, 32, 8, 2, 7),       # one tile, the window its second half
+    (65, 8, 8, 2, 7),        # a one-key second tile
+    (127, 32, 6, 2, 7),      # three heads per group
+    (191, 32, 8, 2, 7),      # three tiles: an odd count
+    (255, 31, 8, 2, 5),
+    (256, 32, 8, 2, 7),      # the ring exactly full
+    (257, 32, 8, 2, 7),      # its first reuse, one key
+    (385, 33, 4, 2, 7),      # two row tiles per head, the second with one row
+    (513, 64, 8, 2, 3),      # eight row tiles, two per head
+    (642, 96, 4, 2, 7),      # three row tiles per head
+    (900, 128, 2, 1, 7),     # four row tiles per head
+    (1345, 32, 16, 2, 7),    # eight heads per group
+    (1500, 65, 2, 2, 1),     # one head per group, no pooling
+    (2300, 32, 8, 1, 13),    # split keys (several parts)
+]
+
+
+@pytest.mark.parametrize("L,w,hq,hkv,pool", SHAPES, ids=[f"L{s[0]}_w{s[1]}_{s[2]}x{s[3]}_p{s[4]}" for s in SHAPES])
+def test_window_tile_edges(L, w, hq, hkv, pool, monkeypatch):
+    monkeypatch.setenv("RKV_FORCE_WINDOW", "1")
+    b = min(L - 1, w + 20)
+    layers = [[gen(31, 0, l, L, w=w, Hq=hq, Hkv=hkv)] for l in range(2)]
+    run_case([OP.SNAPKV, OP.H2O], [b, b], layers, window=w, pool_kernel=pool, label=f"tiles_L{L}_w{w}")
