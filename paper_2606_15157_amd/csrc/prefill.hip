@@ -1481,8 +1481,19 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
   // every slice of a job fits in the resident workgroups; other layouts take the window kernels
   // (window.hip), which the test hook RKV_FORCE_WINDOW=1 selects everywhere
   static const int pipe_wg = resident_pipe_groups();
-  const bool pipe = n_jobs > 0 && row_tiles == 4 && P.force_window == 0 && P.n_slices <= kPipeMaxSlices &&
-                    P.n_slices <= pipe_wg;
+  const bool pipe_fits = n_jobs > 0 && row_tiles == 4 && P.force_window == 0 && P.n_slices <= kPipeMaxSlices &&
+                         P.n_slices <= pipe_wg;
+  // Of those, the window kernels are the faster ones once the chip is full and either
+  //   - rows are padded (fewer than 128, or a window that is no multiple of 32): the pipelined
+  //     kernel then masks every tile (30 layers at L = 4096, two query heads per KV head: 163 us
+  //     a call against 114; 32 jobs of 1024 keys: 30 against 37, so from 128 jobs or 1024 items), or
+  //   - a job has few slices: its two-level exchange is then a large share of an item (30 layers at
+  //     L = 1024: 72 us against 53, batch 8: 373 against 309; at 16 slices 94 against 75, but at 12
+  //     slices and 1920 jobs 389 against 403, and 32 slices are even or better in the pipeline).
+  const bool padded = P.group * ntg < 4 || P.window != 32 * ntg;
+  const bool window_wins = padded ? n_jobs >= 128 || (int64_t)n_jobs * P.n_slices >= 1024
+                                  : n_jobs >= 128 && P.n_slices <= (n_jobs < 1024 ? 16 : 8);
+  const bool pipe = pipe_fits && !window_wins;
   const dim3 prep_grid(n_jobs * kPrepParts), prep_block(kPrepThreads);
   if (pipe) {
     if (ntg == 1) launch_staged(kStageZero, prepare_kernel<1>, prep_grid, prep_block, 0, st, P);

@@ -1,6 +1,7 @@
 """GPU parity of the window scoring kernels at the edges of their tiles: 64-key tiles in a ring of
 four, 32-key subtiles, 128-key slices, four and eight row tiles, one to four row tiles per head,
-padded rows, split keys.  Against the oracle, at the bar of the other prefill tests."""
+padded rows, split keys; and of the calls that the pipelined kernel hands to them (many jobs of few
+slices or with padded rows).  Against the oracle, at the bar of the other prefill tests."""
 import pytest
 
 from oracle import prefill as OP
@@ -33,3 +34,12 @@ def test_window_tile_edges(L, w, hq, hkv, pool, monkeypatch):
     b = min(L - 1, w + 20)
     layers = [[gen(31, 0, l, L, w=w, Hq=hq, Hkv=hkv)] for l in range(2)]
     run_case([OP.SNAPKV, OP.H2O], [b, b], layers, window=w, pool_kernel=pool, label=f"tiles_L{L}_w{w}")
+
+
+@pytest.mark.parametrize("L,w,hq,hkv", [(300, 32, 32, 8), (1100, 32, 32, 8), (300, 27, 16, 8), (700, 32, 8, 8)],
+                         ids=["few_slices", "nine_slices", "padded_window", "padded_heads"])
+def test_many_jobs_take_the_window_kernels(L, w, hq, hkv):
+    """128 jobs: the sizes from which the window kernels take short or padded layouts."""
+    rules = [OP.SNAPKV, OP.H2O] * 8
+    layers = [[gen(32, 0, l, L, w=w, Hq=hq, Hkv=hkv)] for l in range(16)]
+    run_case(rules, [60] * 16, layers, window=w, label=f"many_L{L}_w{w}")
