@@ -43,6 +43,16 @@ __device__ __forceinline__ void dma16s_pair(const char* base, uint32_t off, uint
       : "v"(off), "s"(base + 4096), "s"(lds_base + 4096u)
       : "memory");
 }
+// 4 bytes per lane, likewise: to LDS at lds_base + 4 lane.
+__device__ __forceinline__ void dma4(const void* src, uint32_t lds_base) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
+      "global_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(src), "s"(lds_base)
+      : "memory");
+}
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p);

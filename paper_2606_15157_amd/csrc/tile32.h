@@ -13,6 +13,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lds_dma.h"
 #include "rkv_internal.h"
 
@@ -29,7 +31,7 @@ constexpr int kTile = 64;                            // streamed rows per tile
 constexpr int kTileHalfs = kTile * kHeadDim;         // 16-bit values of a tile
 constexpr int kRing = 4;                             // tile buffers of a workgroup
 constexpr int kTileDma = 4;                          // DMA instructions per wave and tile
-constexpr float kHidden = -1e30f;                    // logit of a hidden pair: its exponential is 0
+constexpr float kHidden = -3.402823466e38f;          // logit of a hidden pair (finite: 0 times it is 0): its exponential is 0
 
 // Workgroup barrier for data handed over through LDS only: this wave's LDS operations retire, then
 // s_barrier; vector memory operations stay in flight.
@@ -43,15 +45,28 @@ __device__ __forceinline__ void tile_barrier() {
 // Rows [row0, row0 + 64) of `rows` ([n][128] bf16) into the tile buffer at LDS address lds; rows
 // from n on repeat row n - 1.  Wave wv of four moves instructions I = wv + 4 u (rows 4 I .. 4 I + 3,
 // 1 KiB each): lane l fills row 4 I + l / 16, chunk position l % 16, with source chunk
-// (l % 16) ^ (row % 16) (row % 16 = 4 wv + l / 16 for every u), the swizzle tile_frag reads.
+// (l % 16) ^ (row % 16) (row % 16 = 4 wv + l / 16 for every u), the swizzle tile_frag reads.  Rows
+// that are not 16-byte aligned (a view into a larger buffer) go through registers: the buffer is
+// then complete at this wave's next tile_barrier, as is every DMA the wave issued earlier, whatever
+// wait_tile counts.
 __device__ __forceinline__ void issue_tile(const uint16_t* rows, int row0, int n, uint32_t lds, int wv) {
   const int lane = threadIdx.x & 63, r4 = 4 * wv + (lane >> 4);
   const uint32_t chunk = (uint32_t)((lane & 15) ^ r4) * 16u;
-  if (row0 + kTile <= n) {
+  const bool aligned = ((uintptr_t)rows & 15) == 0;
+  if (aligned && row0 + kTile <= n) {
     const char* base = reinterpret_cast<const char*>(rows + (size_t)row0 * kHeadDim) + 1024 * wv;
     const uint32_t off = (uint32_t)(lane >> 4) * 256u + chunk;
     dma16s_pair(base, off, lds + 1024u * wv);
     dma16s_pair(base + 8192, off, lds + 1024u * wv + 8192u);
+  } else if (!aligned) {
+#pragma unroll 1
+    for (int u = 0; u < kTileDma; ++u) {
+      const int row = min(row0 + 16 * u + r4, n - 1);
+      u32x4 v;
+      __builtin_memcpy(&v, reinterpret_cast<const char*>(rows + (size_t)row * kHeadDim) + chunk, 16);
+      *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(lds + 1024u * (wv + 4 * u) + 16u * lane) = v;
+    }
+    wait_vmcnt<0>();
   } else {
 #pragma unroll
     for (int u = 0; u < kTileDma; ++u) {
@@ -61,11 +76,37 @@ __device__ __forceinline__ void issue_tile(const uint16_t* rows, int row0, int n
   }
 }
 
-// Waits until a tile's own DMA is in, with `later` tiles (0, 1 or at least 2) issued after it.
+// Waits until a tile's own DMA (kDma instructions a tile) is in, with `later` tiles (0, 1 or at least
+// 2) issued after it.
+template <int kDma>
 __device__ __forceinline__ void wait_tile(int later) {
-  if (later >= 2) wait_vmcnt<2 * kTileDma>();
-  else if (later == 1) wait_vmcnt<kTileDma>();
+  if (later >= 2) wait_vmcnt<2 * kDma>();
+  else if (later == 1) wait_vmcnt<kDma>();
   else wait_vmcnt<0>();
+}
+
+// Runs `body(buffer, t)` for the streamed tiles t = 0 .. n - 1, each in buffer t % kRing (a compile-time
+// constant) after `issue(t, buffer)` requested it with kDma DMA instructions a wave.  Tile t + 3 is
+// requested once every wave is past tile t - 1, whose buffer it takes.
+template <int kDma, typename Issue, typename Body>
+__device__ __forceinline__ void stream_tiles(int n, Issue&& issue, Body&& body) {
+#pragma unroll
+  for (int t = 0; t < kRing - 1; ++t)
+    if (t < n) issue(t, t);
+  auto one = [&](auto buf, int t) __attribute__((always_inline)) {
+    constexpr int b = decltype(buf)::value;
+    wait_tile<kDma>(n - 1 - t);
+    tile_barrier();
+    if (t + kRing - 1 < n) issue(t + kRing - 1, (b + kRing - 1) % kRing);
+    body(buf, t);
+  };
+#pragma unroll 1
+  for (int t = 0; t < n; t += kRing) {
+    one(std::integral_constant<int, 0>{}, t);
+    if (t + 1 < n) one(std::integral_constant<int, 1>{}, t + 1);
+    if (t + 2 < n) one(std::integral_constant<int, 2>{}, t + 2);
+    if (t + 3 < n) one(std::integral_constant<int, 3>{}, t + 3);
+  }
 }
 
 // Byte offset inside a tile of this lane's fragment of k-step st (rows sub * 32 + lane % 32, 16-byte
@@ -142,6 +183,11 @@ __device__ __forceinline__ void tile_step(const uint16_t* tile, uint32_t tl, int
 // Sums that only a later iteration reads: without this the compiler sinks the additions, and the
 // exponentials that feed them, out of the MFMA steps they are interleaved with.
 __device__ __forceinline__ void keep_here(float (&z)[2]) { asm volatile("" : "+v"(z[0]), "+v"(z[1])); }
+// x plus the value of another lane of its 16-lane row.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+}
 // The value of lane ^ 1.
 __device__ __forceinline__ float dpp_pair(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false));
@@ -158,6 +204,19 @@ __device__ __forceinline__ void hide_all(f32x16 (&a)[2]) {
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[b][i] = kHidden;
+}
+
+// Work item of a grid with `per_job` workgroups for each of n_jobs jobs whose workgroups stream the same
+// rows; item 0 of every job is its longest.  by_job: eight jobs at a time, one per XCD (workgroups go round
+// the eight XCDs), so that a job's rows are fetched into one L2 cache; otherwise the longest items of all
+// jobs come first, which ends the launch evenly.
+struct JobItem {
+  int job, item;
+};
+__device__ __forceinline__ JobItem job_item(int block, int n_jobs, int per_job, bool by_job) {
+  if (!by_job) return {block % n_jobs, block / n_jobs};
+  const int first = block / (8 * per_job) * 8, r = block - first * per_job, n = min(8, n_jobs - first);
+  return {first + r % n, r / n};
 }
 
 }  // namespace

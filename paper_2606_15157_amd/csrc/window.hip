@@ -38,8 +38,6 @@
 
 #include <math.h>
 
-#include <type_traits>
-
 #include "tile32.h"
 
 namespace rkv {
@@ -61,31 +59,14 @@ __device__ __forceinline__ WinRow win_row(int r, int tpr, int G, int w) {
   return x;
 }
 
-// Runs `body(buffer, t)` for the tiles t = 0 .. n - 1 (key tile kt0 + kDir t) of the key head, each with
-// its tile in sK[buffer]; the buffer is a compile-time constant.  Tile t + 3 is requested once every
-// wave is past tile t - 1, whose buffer it takes.
+// The key tiles kt0 + kDir t, t = 0 .. n - 1, of a key head through the ring.
 template <int kDir, typename Body>
 __device__ __forceinline__ void stream_keys(const uint16_t* khead, int L, int kt0, int n, uint16_t (*sK)[kTileHalfs],
                                             int wv, Body&& body) {
   const uint32_t lds0 = lds_addr(&sK[0][0]);
-#pragma unroll
-  for (int t = 0; t < kRing - 1; ++t)
-    if (t < n) issue_tile(khead, (kt0 + kDir * t) * kTile, L, lds0 + t * (kTileHalfs * 2), wv);
-  auto one = [&](auto buf, int t) __attribute__((always_inline)) {
-    constexpr int b = decltype(buf)::value;
-    wait_tile(n - 1 - t);
-    tile_barrier();
-    if (t + kRing - 1 < n)
-      issue_tile(khead, (kt0 + kDir * (t + kRing - 1)) * kTile, L, lds0 + ((b + kRing - 1) % kRing) * (kTileHalfs * 2), wv);
-    body(buf, t);
-  };
-#pragma unroll 1
-  for (int t = 0; t < n; t += kRing) {
-    one(std::integral_constant<int, 0>{}, t);
-    if (t + 1 < n) one(std::integral_constant<int, 1>{}, t + 1);
-    if (t + 2 < n) one(std::integral_constant<int, 2>{}, t + 2);
-    if (t + 3 < n) one(std::integral_constant<int, 3>{}, t + 3);
-  }
+  stream_tiles<kTileDma>(n, [&](int t, int buf) __attribute__((always_inline)) {
+    issue_tile(khead, (kt0 + kDir * t) * kTile, L, lds0 + buf * (kTileHalfs * 2), wv);
+  }, body);
 }
 
 template <int NRT>
