@@ -137,13 +137,8 @@ __device__ __forceinline__ void causal_rows(const uint16_t* qgroup, int n_q, con
   }
   add_sums();
   turn();
-  // the sum over the lane halves: lane half hf has block hf
-  auto halves = [&](const double (&a)[2]) {
-    const double other = __shfl_xor(hf ? a[0] : a[1], 32);
-    return (hf ? a[1] : a[0]) + other;
-  };
-  sm.z[kg][64 * rg + lane] = halves(Z);
-  if constexpr (kMoment) sm.t[kg][64 * rg + lane] = halves(T);
+  sm.z[kg][64 * rg + lane] = halves_sum(Z);
+  if constexpr (kMoment) sm.t[kg][64 * rg + lane] = halves_sum(T);
   tile_barrier();
 }
 

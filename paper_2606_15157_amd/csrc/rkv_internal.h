@@ -68,9 +68,9 @@ struct PrefillLaunch {
   float* stats;           // [J][n_slices][128]  pipelined kernel: per-slice row sums (NaN until stored);
                           // [J][window_parts][R]  window kernels with several parts: partial row sums
   float* part;            // [J][kPipeGroups][128]  pipelined kernel: per-group sums of those (NaN until stored)
-  float* lam;             // [J][R]  window kernels: per-row log2 softmax normaliser (+inf for padding rows)
+  float* lam;             // [J][R]  window kernels with one part: row sums relative to the reference
   float* ncl;             // [J][128]  pipelined kernel: minus the per-row reference logit (0 for padding rows);
-                          // [J][R]  window kernels with several parts: the reference in log2 units (+inf: padding)
+                          // [J][R]  window kernels: the reference logit (+inf: padding)
   float* lamf;            // [J_full][G][L]  full-span H2O: log2 normaliser of every query row
   float* tz;              // [J_tova][G][L]  TOVA: log2-scaled logits of the last query per head
   float* tstat;           // [J_tova][n_slices][G][2]  TOVA: per-slice (max, sum of exp2(x - max))

@@ -180,6 +180,68 @@ __device__ __forceinline__ void tile_step(const uint16_t* tile, uint32_t tl, int
   }
 }
 
+// The same with 16x16x32 MFMA: the wave's rows are four blocks of 16 (own[b][st]: row lane % 16, chunk 4 st +
+// lane / 16), the streamed subtile two of 16.  Register i of acc[kh][b] is row 4 (lane / 16) + i of the A
+// operand (block b, or part kh of the subtile with kStreamA), its column row lane % 16 of the other.  Half as
+// many roundings of a logit as with 32x32x16, for twice the MFMA issue.  Values are numbered
+// u = 16 kh + 4 b + i.
+__device__ __forceinline__ uint32_t tile_lane16() {
+  const uint32_t r = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3;
+  return r * 256u + (r ^ lg) * 16u;
+}
+__device__ __forceinline__ void load_block16(const uint16_t* row, bf16x8 (&f)[4]) {
+  const int lg = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (row) v = *reinterpret_cast<const u32x4*>(row + 8 * (4 * st + lg));
+    f[st] = __builtin_bit_cast(bf16x8, v);
+  }
+}
+// Dot product of this lane's row with another row in memory, over the row's four lane groups.
+__device__ __forceinline__ float block_dot16(const bf16x8 (&f)[4], const uint16_t* row) {
+  const int lg = (threadIdx.x >> 4) & 3;
+  float a = 0.f;
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    const u32x4 x = *reinterpret_cast<const u32x4*>(row + 8 * (4 * st + lg));
+    const u32x4 y = __builtin_bit_cast(u32x4, f[st]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x[u]), __builtin_bit_cast(bf16x2, y[u]), a, false);
+  }
+  a += __shfl_xor(a, 16);
+  return a + __shfl_xor(a, 32);
+}
+template <bool kStreamA, typename Value>
+__device__ __forceinline__ void tile_step16(const uint16_t* tile, uint32_t tl, int sub, const bf16x8 (&own)[4][4],
+                                            f32x4 (&acc)[2][4], Value&& value) {
+  auto frag = [&](int j) __attribute__((always_inline)) {   // (kh, st) = (j / 4, j % 4)
+    return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(tile) + (tl ^ (64u * (j & 3))) + 4096u * (j >> 2) + 8192u * sub);
+  };
+  bf16x8 f[3];
+  f[0] = frag(0);
+  f[1] = frag(1);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) value(u);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j + 2 < 8) f[(j + 2) % 3] = frag(j + 2);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f}, c = (j & 3) == 0 ? z : acc[j >> 2][b];
+      acc[j >> 2][b] = kStreamA ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j % 3], own[b][j & 3], c, 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(own[b][j & 3], f[j % 3], c, 0, 0, 0);
+    }
+    if (j < 7) {
+#pragma unroll
+      for (int u = 4 * j + 4; u < 4 * j + 8; ++u) value(u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Sums that only a later iteration reads: without this the compiler sinks the additions, and the
 // exponentials that feed them, out of the MFMA steps they are interleaved with.
 __device__ __forceinline__ void keep_here(float (&z)[2]) { asm volatile("" : "+v"(z[0]), "+v"(z[1])); }
@@ -193,10 +255,17 @@ __device__ __forceinline__ float dpp_pair(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false));
 }
 
-// c + log2(z) for z >= 1.  The logarithm is taken of the mantissa: of z itself (a row sum in the
-// thousands) its last bit is 1e-6, an error that all rows of like sums share.
+// The sums of a wave's 64 rows over the two lane halves: lane half hf returns block hf's.
+__device__ __forceinline__ double halves_sum(const double (&a)[2]) {
+  const int hf = (threadIdx.x >> 5) & 1;
+  const double other = __shfl_xor(hf ? a[0] : a[1], 32);
+  return (hf ? a[1] : a[0]) + other;
+}
+
+// c + log2(z) for z >= 1, rounded once.  The logarithm is taken of the mantissa: of z itself (a row sum
+// in the thousands) its last bit is 1e-6, an error that all rows of like sums share.
 __device__ __forceinline__ float add_log2(float c, float z) {
-  return (c + (float)__builtin_amdgcn_frexp_expf(z)) + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(z));
+  return (float)((double)c + (double)__builtin_amdgcn_frexp_expf(z) + (double)__builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(z)));
 }
 
 __device__ __forceinline__ void hide_all(f32x16 (&a)[2]) {

@@ -13,20 +13,22 @@
 //
 // window_rows_kernel<NRT>: one workgroup per job (per part of its keys when there are few jobs:
 //   the columns kernel then adds the parts' row sums).  The keys are the A operand, so a lane holds
-//   one window row and sixteen keys, and its row sum and reference are one register each: e =
+//   one window row of each block and some keys, and the row's sum and reference are one register each: e =
 //   exp2((z - c_r) log2(e) / sqrt(d)) against a fixed per-row reference c_r = max(logit with the
-//   row's own key, logit with key 0).  The row's log2 normaliser Lambda_r = c_r log2(e)/sqrt(d) +
-//   log2(Z_r) goes to the workspace; a row whose sum overflows (a key more than ~88 natural-log
-//   units above its reference) marks the part, and the columns kernel flags the job for the exact
-//   rescoring of the selection kernels.
+//   row's own key, logit with key 0).  c_r and the row sum go to the workspace; a row whose sum overflows (a
+//   key more than ~88 natural-log units above its reference) marks the part, and the columns kernel
+//   flags the job for the exact rescoring of the selection kernels.
 // window_cols_kernel<NRT>: one workgroup per (job, range of 128-key slices).  The window rows are
-//   the A operand, so a lane holds one key and sixteen rows of each block, with their normalisers in
-//   registers; p = exp2(z log2(e)/sqrt(d) - Lambda_r) is summed over a block's rows in registers and
+//   the A operand, so a lane holds one key and some rows of each block, with two numbers of each row in
+//   registers; its probabilities are summed over a block's rows in registers and
 //   the per-head column sums give the slice's pooled and unpooled scores and slice-edge sums in
 //   the layout of the pipelined kernel, so the same selection (with its slice-border pool repair)
 //   follows.  Jobs, ranges and tiles run in the reverse of the rows kernel's order, so that the keys it
 //   read last are still in the 256 MB last-level cache.
 // Sums run in a fixed order (the only atomic sets a status bit): results are reproducible.
+//
+// Either kernel takes its logits from 32x32x16 MFMA or, for the prompts that the pipelined kernel could take,
+// from 16x16x32 (fewer roundings).
 //
 // Bound: issue of the exponentials and MFMAs (per 64 logits 16 cycles of multiply-add, exponential
 // and addition, beside 16 of the matrix pipe, half of which hold back the VALU too), at the clock the
@@ -69,13 +71,105 @@ __device__ __forceinline__ void stream_keys(const uint16_t* khead, int L, int kt
   }, body);
 }
 
-template <int NRT>
+// How the rows kernel takes a wave's 64 window rows: the keys are the A operand, so a lane holds one row of each
+// block (kBlocks blocks of kRows rows) and some keys, and the row's reference and sums are one register each.
+// Sums: a subtile's exponentials by themselves first, then those of a turn of the ring, and the turns in
+// double precision, so the rounding of many small terms added to a large one stays out of them.
+//
+// WideSums, 32x32x16 MFMA: e = exp2(x), x = z log2(e)/sqrt(d) - c log2(e)/sqrt(d).
+struct WideSums {
+  static constexpr int kBlocks = 2, kRows = 32;
+  f32x16 acc[2][2];   // two subtiles in flight
+  bf16x8 q[2][8];
+  int last[2];        // last visible key
+  float nc[2], zs[2][4], Zr[2], sl2;
+  double Z[2];
+  __device__ __forceinline__ void load(int b, const uint16_t* row) { load_block(row, q[b]); }
+  __device__ __forceinline__ float dot(int b, const uint16_t* key) const { return block_dot(q[b], key); }
+  __device__ __forceinline__ void reference(int b, float c) { nc[b] = -c * sl2; }
+  template <int X>
+  __device__ __forceinline__ void hide() { hide_all(acc[X]); }
+  template <int X>
+  __device__ __forceinline__ void exps(int u) {
+    const int b = u >> 4, i = u & 15;
+    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][b][i], sl2, nc[b]));
+    if (i < 4) zs[b][i] = e;
+    else zs[b][i & 3] += e;
+  }
+  template <int X>   // a subtile into acc[X], beside the exponentials of acc[1 - X]
+  __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
+    tile_step<true>(tile, tile_lane(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+  }
+  template <int X>   // hides the keys of a subtile at k0 past a row's position (or the prompt)
+  __device__ __forceinline__ void mask(int k0) {
+    const int hf = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + acc_row(i) + 4 * hf > last[b]) acc[X][b][i] = kHidden;
+  }
+  __device__ __forceinline__ void keep() { keep_here(Zr); }
+  // the wave's row sums, over the lanes of a row, to out[0 .. 63]
+  __device__ __forceinline__ void put(double* out) const { out[threadIdx.x & 63] = halves_sum(Z); }
+};
+// FineSums, 16x16x32 MFMA: the same, with half as many roundings of z (see FineRows).
+struct FineSums {
+  static constexpr int kBlocks = 4, kRows = 16;
+  f32x4 acc[2][2][4];
+  bf16x8 q[4][4];
+  int last[4];
+  float nc[4], zs[4][4], Zr[4], sl2;
+  double Z[4];
+  __device__ __forceinline__ void load(int b, const uint16_t* row) { load_block16(row, q[b]); }
+  __device__ __forceinline__ float dot(int b, const uint16_t* key) const { return block_dot16(q[b], key); }
+  __device__ __forceinline__ void reference(int b, float c) { nc[b] = -c * sl2; }
+  template <int X>
+  __device__ __forceinline__ void hide() {
+#pragma unroll
+    for (int u = 0; u < 32; ++u) acc[X][u >> 4][(u >> 2) & 3][u & 3] = kHidden;
+  }
+  template <int X>
+  __device__ __forceinline__ void exps(int u) {
+    const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
+    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][kh][b][i], sl2, nc[b]));
+    if (kh == 0) zs[b][i] = e;
+    else zs[b][i] += e;
+  }
+  template <int X>
+  __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
+    tile_step16<true>(tile, tile_lane16(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+  }
+  template <int X>
+  __device__ __forceinline__ void mask(int k0) {
+    const int lg = (threadIdx.x >> 4) & 3;
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+      const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
+      if (k0 + 16 * kh + 4 * lg + i > last[b]) acc[X][kh][b][i] = kHidden;
+    }
+  }
+  __device__ __forceinline__ void keep() { asm volatile("" : "+v"(Zr[0]), "+v"(Zr[1]), "+v"(Zr[2]), "+v"(Zr[3])); }
+  __device__ __forceinline__ void put(double* out) const {   // lane group lg ends with block lg
+    const int lane = threadIdx.x & 63;
+    double s = 0.0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      double z = Z[b] + __shfl_xor(Z[b], 16);
+      z += __shfl_xor(z, 32);
+      if (lane >> 4 == b) s = z;
+    }
+    out[lane] = s;
+  }
+};
+
+template <int NRT, typename Rows>
 __global__ __launch_bounds__(256, 2) void window_rows_kernel(const PrefillLaunch P) {
   constexpr int R = NRT * 32, RG = NRT / 2, KG = 4 / RG;   // row groups of 64, key groups of a tile
   __shared__ __attribute__((aligned(16))) uint16_t sK[kRing][kTileHalfs];
-  __shared__ float sZ[KG][R];
+  __shared__ double sZ[KG][R];
   __shared__ float sC[R];
-  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wv % RG, kg = wv / RG;
   const int L = P.seq_len, w = P.window, G = P.group, Hq = P.n_q_heads, Hkv = P.n_kv_heads, B = P.batch;
   const int tpr = P.row_tiles_per_group * 32;
@@ -88,89 +182,80 @@ __global__ __launch_bounds__(256, 2) void window_rows_kernel(const PrefillLaunch
   const int n_tiles = (L + kTile - 1) / kTile, per_part = (n_tiles + parts - 1) / parts;
   const int t0 = min(n_tiles, part * per_part), n = min(n_tiles, t0 + per_part) - t0;
 
-  // the wave's rows 64 rg + 32 b + l32, their references and last visible keys
-  bf16x8 q[2][8];
-  float ncs[2], Z[2] = {0.f, 0.f};
-  int last[2];
-  const float sl2 = P.scale_log2;
+  // the wave's rows 64 rg .., their references and last visible keys
+  Rows rows;
+  rows.sl2 = P.scale_log2;
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const WinRow x = win_row(64 * rg + 32 * b + l32, tpr, G, w);
-    load_block(x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr, q[b]);
-    last[b] = x.valid ? L - w + x.ii : L - 1;
-    const float c = fmaxf(block_dot(q[b], khead + (size_t)last[b] * kHeadDim), block_dot(q[b], khead));
-    if (kg == 0 && hf == 0) sC[64 * rg + 32 * b + l32] = c;
-    ncs[b] = -c * sl2;
+  for (int b = 0; b < Rows::kBlocks; ++b) {
+    const int r = 64 * rg + Rows::kRows * b + lane % Rows::kRows;
+    const WinRow x = win_row(r, tpr, G, w);
+    rows.load(b, x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr);
+    rows.last[b] = x.valid ? L - w + x.ii : L - 1;
+    const float c = fmaxf(rows.dot(b, khead + (size_t)rows.last[b] * kHeadDim), rows.dot(b, khead));
+    if (kg == 0 && lane < Rows::kRows) sC[r] = c;
+    rows.reference(b, c);
+    rows.Z[b] = 0.0;
+    rows.Zr[b] = 0.f;
   }
-  f32x16 accA[2], accB[2];
-  hide_all(accB);
-  const uint32_t tl = tile_lane();
-  // a subtile's exponentials are summed by themselves first: the row sums then take an addition per
-  // subtile, and the rounding of many small terms added to a large one stays out of them
-  float zs[2][2];
-  auto exps = [&](const f32x16 (&v)[2], int u) __attribute__((always_inline)) {
-    const int b = u >> 4, i = u & 15;
-    const float e = __builtin_amdgcn_exp2f(fmaf(v[b][i], sl2, ncs[b]));
-    if (i < 2) zs[b][i] = e;
-    else zs[b][i & 1] += e;
+  rows.template hide<1>();
+  auto add_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < Rows::kBlocks; ++b) rows.Zr[b] += (rows.zs[b][0] + rows.zs[b][1]) + (rows.zs[b][2] + rows.zs[b][3]);
   };
-  // a subtile of keys k0 .. k0 + 31, with the exponentials of the one before it
-  auto step = [&](const uint16_t* tile, int sub, int k0, f32x16 (&cur)[2], const f32x16 (&prev)[2]) __attribute__((always_inline)) {
-    tile_step<true>(tile, tl, sub, q, cur, [&](int u) __attribute__((always_inline)) { exps(prev, u); });
+  auto turn = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) Z[b] += zs[b][0] + zs[b][1];
-    keep_here(Z);
-    if (k0 + 31 > L - w) {   // keys past a row's position (or the prompt) take no part
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (k0 + acc_row(i) + 4 * hf > last[b]) cur[b][i] = kHidden;
+    for (int b = 0; b < Rows::kBlocks; ++b) {
+      rows.Z[b] += (double)rows.Zr[b];
+      rows.Zr[b] = 0.f;
     }
   };
+  // a subtile of keys k0 .. k0 + 31 into accumulators X, with the exponentials of the one before it
+  auto step = [&](auto X, const uint16_t* tile, int sub, int k0) __attribute__((always_inline)) {
+    constexpr int x = decltype(X)::value;
+    rows.template step<x>(tile, sub);
+    add_sums();
+    rows.keep();
+    if (k0 + 31 > L - w) rows.template mask<x>(k0);
+  };
+  const std::integral_constant<int, 0> kA{};
+  const std::integral_constant<int, 1> kB{};
   stream_keys<1>(khead, L, t0, n, sK, wv, [&](auto buf, int t) __attribute__((always_inline)) {
     constexpr int b = decltype(buf)::value;
     const int k0 = (t0 + t) * kTile;
     if constexpr (KG == 1) {
-      step(sK[b], 0, k0, accA, accB);
-      step(sK[b], 1, k0 + 32, accB, accA);
+      step(kA, sK[b], 0, k0);
+      step(kB, sK[b], 1, k0 + 32);
     } else if constexpr ((b & 1) == 0) {
-      step(sK[b], kg, k0 + 32 * kg, accA, accB);
+      step(kA, sK[b], kg, k0 + 32 * kg);
     } else {
-      step(sK[b], kg, k0 + 32 * kg, accB, accA);
+      step(kB, sK[b], kg, k0 + 32 * kg);
     }
+    if constexpr (b == kRing - 1) turn();
   });
   if (KG == 1 || (n & 1) == 0) {
 #pragma unroll
-    for (int u = 0; u < 32; ++u) exps(accB, u);
+    for (int u = 0; u < 32; ++u) rows.template exps<1>(u);
   } else {
 #pragma unroll
-    for (int u = 0; u < 32; ++u) exps(accA, u);
+    for (int u = 0; u < 32; ++u) rows.template exps<0>(u);
   }
   // sums over the lane halves and the key groups; the row's log2 normaliser (one part), or the part's
   // row sum and, from part 0, the reference (several parts: the columns kernel adds them)
-#pragma unroll
-  for (int b = 0; b < 2; ++b) Z[b] += zs[b][0] + zs[b][1];
-  {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(Z[0]), __float_as_uint(Z[1]), false, false);
-    sZ[kg][64 * rg + lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane half hf has block hf
-  }
+  add_sums();
+  turn();
+  rows.put(&sZ[kg][64 * rg]);
   tile_barrier();
   bool over = false;
   if (tid < R) {
     const WinRow x = win_row(tid, tpr, G, w);
-    float z = sZ[0][tid];
+    double zd = sZ[0][tid];
 #pragma unroll
-    for (int k = 1; k < KG; ++k) z += sZ[k][tid];
+    for (int k = 1; k < KG; ++k) zd += sZ[k][tid];
+    const float z = (float)zd;
     over = x.valid && !(z < __builtin_inff());   // a key far above the row's reference
-    const float c = sC[tid] * sl2;
-    if (parts == 1) {
-      // padding and overflowing rows: +inf, every probability 0
-      P.lam[(size_t)job * R + tid] = x.valid && z < __builtin_inff() ? add_log2(c, z) : __builtin_inff();
-    } else {
-      P.stats[((size_t)job * parts + part) * R + tid] = z;
-      if (part == 0) P.ncl[(size_t)job * R + tid] = x.valid ? c : __builtin_inff();
-    }
+    if (part == 0) P.ncl[(size_t)job * R + tid] = x.valid ? sC[tid] : __builtin_inff();
+    if (parts == 1) P.lam[(size_t)job * R + tid] = z;
+    else P.stats[((size_t)job * parts + part) * R + tid] = z;
   }
   // The part's overflow mark, for the columns kernel; it also starts the call's status word.
   const int any = __syncthreads_or(over);
@@ -180,7 +265,134 @@ __global__ __launch_bounds__(256, 2) void window_rows_kernel(const PrefillLaunch
   }
 }
 
-template <int NRT>
+// How the columns kernel takes a wave's 64 window rows: they are the A operand, so a lane holds one key and some
+// rows of each block, and two numbers of every row, made of its reference logit c and its row sum z.
+//
+// WideRows, 32x32x16 MFMA: p = exp2(x), x = z_rj log2(e)/sqrt(d) - Lambda_r, the row's log2 normaliser.
+struct WideRows {
+  f32x16 acc[2][2];   // two subtiles in flight
+  bf16x8 q[2][8];
+  f32x4 nl[2][4];     // -Lambda
+  float cs[2][4];     // column sums of a block
+  float sl2;
+  static __device__ __forceinline__ float2 numbers(float c, float z, float sl2) { return {-add_log2(c * sl2, z), 0.f}; }
+  template <typename Row>   // row(r): the wave's row r (0 .. 63) in memory, or null
+  __device__ __forceinline__ void load(Row&& row) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) load_block(row(32 * b + (int)(threadIdx.x & 31)), q[b]);
+  }
+  __device__ __forceinline__ void stats(const float* a, const float*) {
+    const int hf = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) nl[b][u] = *reinterpret_cast<const f32x4*>(a + 32 * b + 8 * u + 4 * hf);
+  }
+  template <int X>
+  __device__ __forceinline__ void hide() { hide_all(acc[X]); }
+  template <int X>
+  __device__ __forceinline__ void exps(int u) {
+    const int b = u >> 4, i = u & 15;
+    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][b][i], sl2, nl[b][i >> 2][i & 3]));
+    if (i < 4) cs[b][i] = e;
+    else cs[b][i & 3] += e;
+  }
+  template <int X>   // a subtile into acc[X], beside the exponentials of acc[1 - X]
+  __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
+    tile_step<false>(tile, tile_lane(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+  }
+  template <int X, typename Seen>   // seen(key of the subtile, row): hides the others
+  __device__ __forceinline__ void mask(Seen&& seen) {
+    const int l32 = threadIdx.x & 31, hf = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (!seen(l32, b, acc_row(i) + 4 * hf)) acc[X][b][i] = kHidden;
+  }
+  // column sums of the subtile to sum0 (the wave's first row tile) and sum1, of both to sum0 if `pair`
+  __device__ __forceinline__ void put(float* sum0, float* sum1, bool pair) const {
+    const int l32 = threadIdx.x & 31, hf = (threadIdx.x >> 5) & 1;
+    const float c0 = (cs[0][0] + cs[0][1]) + (cs[0][2] + cs[0][3]), c1 = (cs[1][0] + cs[1][1]) + (cs[1][2] + cs[1][3]);
+    if (pair) {
+      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0 + c1), __float_as_uint(c0 + c1), false, false);
+      if (hf == 0) sum0[l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    } else {
+      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0), __float_as_uint(c1), false, false);
+      (hf ? sum1 : sum0)[l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane half hf: block hf
+    }
+  }
+};
+// FineRows, 16x16x32 MFMA: p = exp2(x) w_r, x = z_rj log2(e)/sqrt(d) - c_r log2(e)/sqrt(d), with the weight
+// w_r = 1 / z_r, so that no number of the size of Lambda is rounded, and a logit is rounded half as often:
+// the accuracy of the pipelined kernel for about 4 % more time (batch 3, L = 3331, w = 27, two heads a group:
+// error 1.54e-7 -> 1.37e-7 and a call 93 -> 97 us; the pipelined kernel 1.25e-7 and 113 us).
+struct FineRows {
+  f32x4 acc[2][2][4];
+  bf16x8 q[4][4];
+  f32x4 nc[4], wt[4];   // -c log2(e)/sqrt(d), w
+  float cs[2][2];       // column sums of a key half and row tile
+  float sl2;
+  static __device__ __forceinline__ float2 numbers(float c, float z, float sl2) {
+    return {-c * sl2, c < __builtin_inff() ? 1.f / z : 0.f};
+  }
+  template <typename Row>
+  __device__ __forceinline__ void load(Row&& row) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) load_block16(row(16 * b + (int)(threadIdx.x & 15)), q[b]);
+  }
+  __device__ __forceinline__ void stats(const float* a, const float* w) {
+    const int lg = (threadIdx.x >> 4) & 3;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      nc[b] = *reinterpret_cast<const f32x4*>(a + 16 * b + 4 * lg);
+      wt[b] = *reinterpret_cast<const f32x4*>(w + 16 * b + 4 * lg);
+    }
+  }
+  template <int X>
+  __device__ __forceinline__ void hide() {
+    mask<X>([](int, int, int) { return false; });
+  }
+  template <int X>
+  __device__ __forceinline__ void exps(int u) {
+    const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
+    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][kh][b][i], sl2, nc[b][i]));
+    if ((u & 7) == 0) cs[kh][b >> 1] = e * wt[b][i];
+    else cs[kh][b >> 1] = fmaf(e, wt[b][i], cs[kh][b >> 1]);
+  }
+  template <int X>
+  __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
+    tile_step16<false>(tile, tile_lane16(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+  }
+  template <int X, typename Seen>
+  __device__ __forceinline__ void mask(Seen&& seen) {
+    const int l16 = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3;
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+      const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
+      if (!seen(16 * kh + l16, b >> 1, 16 * (b & 1) + 4 * lg + i)) acc[X][kh][b][i] = kHidden;
+    }
+  }
+  __device__ __forceinline__ void put(float* sum0, float* sum1, bool pair) const {
+    // over the four lane groups of a key: lane group lg then has key half lg / 2 and row tile lg % 2
+    auto half = [&](float a, float b) __attribute__((always_inline)) {
+      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+      return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    };
+    const int l16 = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3, k = 16 * (lg >> 1) + l16;
+    if (pair) {
+      const float c = half(cs[0][0] + cs[0][1], cs[1][0] + cs[1][1]);
+      const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(c), false, false);
+      if ((lg & 1) == 0) sum0[k] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    } else {
+      const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(half(cs[0][0], cs[1][0])),
+                                                      __float_as_uint(half(cs[0][1], cs[1][1])), false, false);
+      ((lg & 1) ? sum1 : sum0)[k] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+  }
+};
+
+template <int NRT, typename Rows>
 __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch P) {
   constexpr int R = NRT * 32, NT = 256, RG = NRT / 2, KG = 4 / RG;
   __shared__ __attribute__((aligned(16))) uint16_t sK[kRing][kTileHalfs];
@@ -188,8 +400,8 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
   // 64-row pair of blocks (an even number: both belong to one head); two slices in flight
   constexpr int kPad = 4, kColRow = kSlice + 2 * kPad;   // rows with a zero margin at both ends
   __shared__ float sCol[2][NRT][kColRow];
-  __shared__ __attribute__((aligned(16))) float sLam[R];
-  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  __shared__ __attribute__((aligned(16))) float sA[R], sB[R];   // the rows' numbers
+  const int tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wv % RG, kg = wv / RG;
   const int L = P.seq_len, w = P.window, G = P.group, Hq = P.n_q_heads, Hkv = P.n_kv_heads, B = P.batch;
   const int nsl = P.n_slices, NTH = P.row_tiles_per_group, tpr = NTH * 32;
@@ -220,51 +432,32 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
     const int o = tid % (2 * kPad);
     (&sCol[0][0][0])[tid / (2 * kPad) * kColRow + (o < kPad ? o : kSlice + o)] = 0.f;
   }
-  if (P.window_parts == 1) {
-    if (tid < R) sLam[tid] = P.lam[(size_t)job * R + tid];
-  } else if (tid < R) {
-    // the parts' row sums, added in part order; +inf for padding and overflowing rows
-    const int parts = P.window_parts;
-    const float c = P.ncl[(size_t)job * R + tid];
-    float z = 0.f;
-    for (int p = 0; p < parts; ++p) z += P.stats[((size_t)job * parts + p) * R + tid];
-    sLam[tid] = c < __builtin_inff() && z < __builtin_inff() ? add_log2(c, z) : __builtin_inff();
-  }
-  bf16x8 q[2][8];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const WinRow x = win_row(64 * rg + 32 * b + l32, tpr, G, w);
-    load_block(x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr, q[b]);
-  }
-  tile_barrier();
-  // minus the normalisers of the rows this lane's accumulators hold
-  f32x4 nl[2][4];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      nl[b][u] = *reinterpret_cast<const f32x4*>(&sLam[64 * rg + 32 * b + 8 * u + 4 * hf]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) nl[b][u][i] = -nl[b][u][i];
-    }
-  float cs[2][2];
-  auto exps = [&](const f32x16 (&v)[2], int u) __attribute__((always_inline)) {
-    const int b = u >> 4, i = u & 15;
-    const float e = __builtin_amdgcn_exp2f(fmaf(v[b][i], sl2, nl[b][i >> 2][i & 3]));
-    if (i < 2) cs[b][i] = e;
-    else cs[b][i & 1] += e;
-  };
-  // the column sums of a subtile: key offset kb of the slice in buffer sb (both constants)
-  auto put = [&](int sb, int kb) __attribute__((always_inline)) {
-    const float c0 = cs[0][0] + cs[0][1], c1 = cs[1][0] + cs[1][1];
-    if (pair) {
-      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0 + c1), __float_as_uint(c0 + c1), false, false);
-      if (hf == 0) sCol[sb][rg][kPad + kb + l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  Rows rows;
+  rows.sl2 = sl2;
+  if (tid < R) {
+    float z;   // the row's sum (several parts: theirs added in part order)
+    if (P.window_parts == 1) {
+      z = P.lam[(size_t)job * R + tid];
     } else {
-      const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0), __float_as_uint(c1), false, false);
-      sCol[sb][2 * rg + hf][kPad + kb + l32] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane half hf: block hf
+      z = 0.f;
+      for (int p = 0; p < P.window_parts; ++p) z += P.stats[((size_t)job * P.window_parts + p) * R + tid];
     }
-  };
+    // padding and overflowing rows: reference +inf, every probability 0
+    float c = P.ncl[(size_t)job * R + tid];
+    if (!(z < __builtin_inff())) {
+      z = 1.f;
+      c = __builtin_inff();
+    }
+    const float2 n = Rows::numbers(c, z, sl2);
+    sA[tid] = n.x;
+    sB[tid] = n.y;
+  }
+  rows.load([&](int r) __attribute__((always_inline)) {
+    const WinRow x = win_row(64 * rg + r, tpr, G, w);
+    return x.valid ? qjob + (size_t)(x.g * w + x.ii) * kHeadDim : nullptr;
+  });
+  tile_barrier();
+  rows.stats(sA + 64 * rg, sB + 64 * rg);
   // Scores of slice b from the column sums in buffer sb.  The common forms (one sCol row per head, no
   // mask border in the slice, a 7-wide pool where pooled) take one wave pair for the keys, every head
   // of a key in one thread, and the other pair for the slice-edge sums.  Their pool windows are cut by
@@ -342,22 +535,25 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
       }
     }
   };
-  const uint32_t tl = tile_lane();
-  f32x16 accA[2], accB[2];
-  hide_all(accB);
-  // the subtile at key ka, beside the exponentials of the one before it, whose sums then go to (sb, kb)
-  auto step = [&](const uint16_t* tile, int sub, int ka, int sb, int kb, f32x16 (&cur)[2], const f32x16 (&prev)[2])
-                  __attribute__((always_inline)) {
-    tile_step<false>(tile, tl, sub, q, cur, [&](int u) __attribute__((always_inline)) { exps(prev, u); });
-    put(sb, kb);
-    if (ka + 31 > L - w) {   // keys past a row's position (or the prompt) take no part
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)   // window index of the block's first row, plus the row in the block
-          if (ka + l32 > L - w + 32 * ((2 * rg + b) % NTH) + acc_row(i) + 4 * hf) cur[b][i] = kHidden;
-    }
+  // the column sums of a subtile: key offset kb of the slice in buffer sb (both constants)
+  auto put = [&](int sb, int kb) __attribute__((always_inline)) {
+    if (pair) rows.put(&sCol[sb][rg][kPad + kb], nullptr, true);
+    else rows.put(&sCol[sb][2 * rg][kPad + kb], &sCol[sb][2 * rg + 1][kPad + kb], false);
   };
+  rows.template hide<1>();
+  // the subtile at key ka into accumulators X, beside the exponentials of the one before it, whose sums then
+  // go to (sb, kb)
+  auto step = [&](auto X, const uint16_t* tile, int sub, int ka, int sb, int kb) __attribute__((always_inline)) {
+    constexpr int x = decltype(X)::value;
+    rows.template step<x>(tile, sub);
+    put(sb, kb);
+    if (ka + 31 > L - w)   // keys past a row's position (or the prompt) take no part
+      rows.template mask<x>([&](int key, int rt, int r) __attribute__((always_inline)) {
+        return ka + key <= L - w + 32 * ((2 * rg + rt) % NTH) + r;   // window index of the row tile's first row, plus r
+      });
+  };
+  const std::integral_constant<int, 0> kA{};
+  const std::integral_constant<int, 1> kB{};
   // Tiles and slices run downwards.  The slice of tile t is in column buffer (t / 2) % 2.  Its last sums are written during the next
   // slice's first tile, so its scores are stored in that slice's second tile, after the barrier; the
   // buffer is written again from the first tile of the slice after that.  (The first step of all puts
@@ -366,17 +562,17 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
     constexpr int b = decltype(buf)::value, pb = (b + kRing - 1) % kRing;   // this tile's buffer, the one before
     const int ka = (2 * b1 - 1 - t) * kTile;
     if constexpr (KG == 1) {
-      step(sK[b], 0, ka, pb / 2, b % 2 * kTile + 32, accA, accB);
-      step(sK[b], 1, ka + 32, b / 2, pb % 2 * kTile, accB, accA);
+      step(kA, sK[b], 0, ka, pb / 2, b % 2 * kTile + 32);
+      step(kB, sK[b], 1, ka + 32, b / 2, pb % 2 * kTile);
     } else if constexpr (b % 2 == 0) {
-      step(sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg, accA, accB);
+      step(kA, sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg);
     } else {
-      step(sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg, accB, accA);
+      step(kB, sK[b], kg, ka + 32 * kg, pb / 2, b % 2 * kTile + 32 * kg);
     }
     if (b % 2 == 1 && t >= 3) store(b1 - t / 2, 1 - b / 2);
   });
 #pragma unroll
-  for (int u = 0; u < 32; ++u) exps(accB, u);   // n is even: the last subtile's
+  for (int u = 0; u < 32; ++u) rows.template exps<1>(u);   // n is even: the last subtile's
   const int sb = (b1 - 1 - b0) & 1;
   put(sb, KG == 1 ? 32 : 32 * kg);
   tile_barrier();
@@ -385,8 +581,16 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
 
 template <int NRT>
 int launch_window_nrt(const PrefillLaunch& P, int n_jobs, hipStream_t st) {
-  window_rows_kernel<NRT><<<n_jobs * P.window_parts, 256, 0, st>>>(P);
-  window_cols_kernel<NRT><<<(unsigned)((int64_t)n_jobs * P.window_ranges), 256, 0, st>>>(P);
+  const unsigned rows = (unsigned)(n_jobs * P.window_parts), cols = (unsigned)((int64_t)n_jobs * P.window_ranges);
+  if constexpr (NRT == 4) {
+    if (P.n_slices <= kPipeMaxSlices) {   // prompts the pipelined kernel could take: FineRows has why
+      window_rows_kernel<NRT, FineSums><<<rows, 256, 0, st>>>(P);
+      window_cols_kernel<NRT, FineRows><<<cols, 256, 0, st>>>(P);
+      return (int)hipGetLastError();
+    }
+  }
+  window_rows_kernel<NRT, WideSums><<<rows, 256, 0, st>>>(P);
+  window_cols_kernel<NRT, WideRows><<<cols, 256, 0, st>>>(P);
   return (int)hipGetLastError();
 }
 
