@@ -10,6 +10,7 @@ librkv.so.  PyTorch provides device memory and the current HIP stream.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 from typing import Sequence
 
 from . import _abi
@@ -152,12 +153,20 @@ class Plan:
         return nb.value
 
 
-def _ptr(t):
-    return t.data_ptr() if t is not None else None
+_DATA_PTR = operator.methodcaller("data_ptr")
 
 
 def _parr(ptrs):
-    return C.cast(_abi.ptr_array(ptrs), C.POINTER(C.c_void_p))
+    """Pointer table of addresses (None or 0: null); it converts to the C side's void**."""
+    return (C.c_void_p * len(ptrs))(*ptrs)
+
+
+def _table(tensors):
+    """Pointer table of a list of tensors (None: null)."""
+    try:
+        return (C.c_void_p * len(tensors))(*map(_DATA_PTR, tensors))
+    except AttributeError:   # some are None
+        return _parr([t.data_ptr() if t is not None else None for t in tensors])
 
 
 def _stream_handle(stream, device):
@@ -191,18 +200,20 @@ def evict_prefill(plan: Plan, q_win, k, v, *, out=None, workspace=None, score_ou
     B, Hkv, L, d = k[0].shape
     Hq = next((q.shape[1] for q in q_win if q is not None), Hkv)
     dev = k[0].device
-    for t in list(k) + list(v) + [q for q in q_win if q is not None]:
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.device != dev:
+    bf16 = torch.bfloat16
+    for t in (*k, *v, *q_win):
+        if t is not None and (t.dtype != bf16 or not t.is_contiguous() or t.device != dev):
             raise ValueError("inputs must be contiguous bf16 tensors on one device")
-    for t in list(k) + list(v):
-        if tuple(t.shape) != (B, Hkv, L, d):
+    kv_shape = (B, Hkv, L, d)
+    for t in (*k, *v):
+        if t.shape != kv_shape:
             raise ValueError("every k / v must have shape [B, Hkv, L, d]")
+    win_shape, full_shape = (B, Hq, plan.window, d), (B, Hq, L, d)
     for q, r in zip(q_win, plan.rules_prefill):
-        rows = L if r == H2O_FULL else plan.window
-        if q is not None and tuple(q.shape) != (B, Hq, rows, d):
+        if q is not None and q.shape != (full_shape if r == H2O_FULL else win_shape):
             raise ValueError("q_win must have shape [B, Hq, w, d] ([B, Hq, L, d] for H2O_FULL layers)")
-    counts = plan.retained_counts(L)
     if out is None:
+        counts = plan.retained_counts(L)
         out = {
             "k_out": [torch.empty((B, Hkv, c, d), dtype=torch.bfloat16, device=dev) for c in counts],
             "v_out": [torch.empty((B, Hkv, c, d), dtype=torch.bfloat16, device=dev) for c in counts],
@@ -234,11 +245,9 @@ class PreparedPrefill:
         B, Hkv, L, d = k[0].shape
         Hq = next((q.shape[1] for q in q_win if q is not None), Hkv)
         self._keep = (q_win, k, v, out, workspace)
-        self._arrays = [_parr([_ptr(q) for q in q_win]), _parr([_ptr(t) for t in k]), _parr([_ptr(t) for t in v]),
-                        _parr([_ptr(t) for t in out["k_out"]]), _parr([_ptr(t) for t in out["v_out"]]),
-                        _parr([_ptr(t) for t in out["idx"]]),
-                        _parr([_ptr(t) for t in out["scores"]]) if "scores" in out else None,
-                        _parr([_ptr(t) for t in out["acc"]]) if "acc" in out else None]
+        self._arrays = [_table(q_win), _table(k), _table(v), _table(out["k_out"]), _table(out["v_out"]), _table(out["idx"]),
+                        _table(out["scores"]) if "scores" in out else None,
+                        _table(out["acc"]) if "acc" in out else None]
         self.io = _abi.PrefillIO(*self._arrays)
         self.shape = _abi.Shape(B, L, Hq, Hkv, d)
         self.plan = plan
@@ -308,8 +317,7 @@ def entropy_profile(q, k, *, stream=None):
     nbytes = C.c_size_t()
     check(_abi.lib().rkv_entropy_workspace_size(C.byref(shape), n, n_q, C.byref(nbytes)))
     ws = torch.empty((max(nbytes.value, 8) + 7) // 8, dtype=torch.float64, device=dev)
-    check(_abi.lib().rkv_entropy_profile(C.byref(shape), n, n_q, _parr([_ptr(t) for t in q]),
-                                         _parr([_ptr(t) for t in k]), C.c_void_p(rows.data_ptr()),
+    check(_abi.lib().rkv_entropy_profile(C.byref(shape), n, n_q, _table(q), _table(k), C.c_void_p(rows.data_ptr()),
                                          C.c_void_p(h.data_ptr()), C.c_void_p(status.data_ptr()),
                                          C.c_void_p(ws.data_ptr()), ws.numel() * 8,
                                          C.c_void_p(_stream_handle(stream, dev))))
@@ -343,8 +351,8 @@ def decode_init_from_prefill(plan: Plan, prefill_out, state=None, *, stream=None
             state["v_cache"].append(torch.empty((B, Hkv, c, d), dtype=torch.bfloat16, device=dev) if live else None)
             state["pos"].append(torch.empty((B, Hkv, c), dtype=torch.int32, device=dev) if live else None)
             state["acc"].append(torch.empty((B, Hkv, c), dtype=torch.float32, device=dev) if r == H2O else None)
-    st = _abi.DecodeState(_parr([_ptr(t) for t in state["k_cache"]]), _parr([_ptr(t) for t in state["v_cache"]]),
-                          _parr([_ptr(t) for t in state["pos"]]), _parr([_ptr(t) for t in state["acc"]]))
+    st = _abi.DecodeState(_table(state["k_cache"]), _table(state["v_cache"]), _table(state["pos"]),
+                          _table(state["acc"]))
     check(_abi.lib().rkv_decode_init_from_prefill(plan.handle, C.byref(call.shape), C.byref(call.io), C.byref(st),
                                                   C.c_void_p(_stream_handle(stream, dev))))
     return state
@@ -362,10 +370,10 @@ def decode_step(plan: Plan, state, q, k, v, position: int, *, victim_out=None, s
     B, Hkv = k[0].shape[0], k[0].shape[1]
     Hq = q[0].shape[1]
     d = k[0].shape[-1]
-    st = _abi.DecodeState(_parr([_ptr(t) for t in state["k_cache"]]), _parr([_ptr(t) for t in state["v_cache"]]),
-                          _parr([_ptr(t) for t in state["pos"]]), _parr([_ptr(t) for t in state["acc"]]))
-    inp = _abi.DecodeInput(_parr([_ptr(t) for t in q]), _parr([_ptr(t) for t in k]), _parr([_ptr(t) for t in v]),
-                           _parr([_ptr(t) for t in victim_out]) if victim_out is not None else None)
+    st = _abi.DecodeState(_table(state["k_cache"]), _table(state["v_cache"]), _table(state["pos"]),
+                          _table(state["acc"]))
+    inp = _abi.DecodeInput(_table(q), _table(k), _table(v),
+                           _table(victim_out) if victim_out is not None else None)
     shape = _abi.Shape(B, 1, Hq, Hkv, d)
     dev = k[0].device
     assert len(q) == len(k) == len(v) == n

@@ -122,10 +122,3 @@ class RkvError(RuntimeError):
 def check(status: int):
     if status != RKV_OK:
         raise RkvError(status, lib().rkv_last_error().decode(errors="replace"))
-
-
-def ptr_array(ptrs):
-    arr = (C.c_void_p * len(ptrs))()
-    for i, p in enumerate(ptrs):
-        arr[i] = p if p else None
-    return arr
