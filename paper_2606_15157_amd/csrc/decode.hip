@@ -19,9 +19,6 @@ namespace {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kDecThreads = 256;
-constexpr int kDecWaves = kDecThreads / 64;
-
 __device__ __forceinline__ bf16x2 as_bf16x2(uint32_t v) { return __builtin_bit_cast(bf16x2, v); }
 
 // Wave reductions by DPP: rotations inside each 16-lane row (every lane of a row ends with the
@@ -76,6 +73,7 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
   return r;
 }
 
+template <int NW>
 __device__ __forceinline__ uint64_t block_reduce_min_u64(uint64_t v, uint64_t* sh) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   v = wave_min_u64(v);
@@ -83,13 +81,13 @@ __device__ __forceinline__ uint64_t block_reduce_min_u64(uint64_t v, uint64_t* s
   __syncthreads();
   uint64_t r = sh[0];
 #pragma unroll
-  for (int i = 1; i < kDecWaves; ++i) r = sh[i] < r ? sh[i] : r;
+  for (int i = 1; i < NW; ++i) r = sh[i] < r ? sh[i] : r;
   __syncthreads();
   return r;
 }
 
 // Block-wide max / sum of G values at once (each value: its waves' results in wave order).
-template <int G>
+template <int G, int NW>
 __device__ __forceinline__ void block_reduce_max_v(float (&v)[G], float* sh) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -102,12 +100,12 @@ __device__ __forceinline__ void block_reduce_max_v(float (&v)[G], float* sh) {
   for (int g = 0; g < G; ++g) {
     float r = sh[g];
 #pragma unroll
-    for (int i = 1; i < kDecWaves; ++i) r = fmaxf(r, sh[i * G + g]);
+    for (int i = 1; i < NW; ++i) r = fmaxf(r, sh[i * G + g]);
     v[g] = r;
   }
   __syncthreads();
 }
-template <int G>
+template <int G, int NW>
 __device__ __forceinline__ void block_reduce_sum_v(float (&v)[G], float* sh) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -120,17 +118,18 @@ __device__ __forceinline__ void block_reduce_sum_v(float (&v)[G], float* sh) {
   for (int g = 0; g < G; ++g) {
     float r = 0.f;
 #pragma unroll
-    for (int i = 0; i < kDecWaves; ++i) r += sh[i * G + g];
+    for (int i = 0; i < NW; ++i) r += sh[i * G + g];
     v[g] = r;
   }
   __syncthreads();
 }
 
-template <int G>
-__global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch D) {
+template <int G, int NT>
+__global__ __launch_bounds__(NT) void decode_kernel(const DecodeLaunch D) {
+  constexpr int NW = NT / 64;
   extern __shared__ float sDyn[];
-  __shared__ float shf[kDecWaves * 8];
-  __shared__ uint64_t shu[kDecWaves];
+  __shared__ float shf[NW * 8];
+  __shared__ uint64_t shu[NW];
   const int tid = threadIdx.x;
   const int Hkv = D.n_kv_heads, B = D.batch;
   const int item = blockIdx.x;
@@ -149,27 +148,27 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
   uint64_t best = ~0ull;
   int victim = -1;
   if (ly.rule == RKV_STREAMING) {
-    for (int e = tid; e < C; e += kDecThreads) {
+    for (int e = tid; e < C; e += NT) {
       const int ps = pos[e];
       if (ps >= D.n_sink) {
         const uint64_t key = ((uint64_t)(uint32_t)ps << 32) | (uint32_t)e;
         best = key < best ? key : best;
       }
     }
-    best = block_reduce_min_u64(best, shu);
+    best = block_reduce_min_u64<NW>(best, shu);
     victim = best == ~0ull ? -1 : (int)(uint32_t)(best & 0xffffffffu);
   } else {
     float* sZ = sDyn;                      // [G][C+1] logits, then probabilities
     float* sAcc = sDyn + (size_t)G * (C + 1);  // [C+1] updated accumulated scores
     // 16 lanes per entry: lane c (= tid % 16) takes the 16-byte chunk c of the head dimension, so
     // a wave's load instruction reads four whole 256-byte rows; lanes hold chunk c of every
-    // query head.  An iteration covers 64 entries, entry base + tid / 16 + 16 j for j = 0..3.
+    // query head.  An iteration covers NT / 4 entries, entry base + tid / 16 + j NT / 16 for j = 0..3.
     const int c16 = tid & 15, rsub = tid >> 4;
     u32x4 qr[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
       qr[g] = reinterpret_cast<const u32x4*>(ly.q + ((size_t)s * D.n_q_heads + h * G + g) * kHeadDim)[c16];
-    constexpr int kBlk = kDecThreads / 4;   // 64 entries per block
+    constexpr int kBlk = NT / 4;   // entries per block
     // two blocks of key rows in flight: block b + 1's loads are outstanding while block b's dot
     // products run, and block b + 2's are issued right after them (two register sets,
     // alternating).  Every load is unconditional (entries past the end read the new token's row,
@@ -177,7 +176,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     auto load_rows = [&](int base, u32x4 (&kv)[4]) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int e = base + rsub + 16 * j;
+        const int e = base + rsub + NT / 16 * j;
         const uint16_t* kr = e < C ? kc + (size_t)e * kHeadDim : knew;
         kv[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kr) + c16);
       }
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     auto process = [&](int base, const u32x4 (&kv)[4]) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int e = base + rsub + 16 * j;
+        const int e = base + rsub + NT / 16 * j;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           float d = 0.f;
@@ -220,28 +219,28 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     // candidate and the score is this step's alone
     const bool tova = ly.rule == RKV_TOVA;
     const int limit = tova ? p : p - ly.recent;
-    // positions and accumulated scores of entries tid + 256 k (k < kDecPre), requested now so
+    // positions and accumulated scores of entries tid + NT k (k < kDecPre), requested now so
     // that they arrive during the reductions and the exponential pass (the key registers are
     // free here); entries past those are read when visited
-    constexpr int kDecPre = 4;
+    constexpr int kDecPre = NT == 256 ? 4 : 2;
     int pre_pos[kDecPre];
     float pre_acc[kDecPre];
 #pragma unroll
     for (int k = 0; k < kDecPre; ++k) {
-      const int e = tid + kDecThreads * k;
+      const int e = tid + NT * k;
       pre_pos[k] = e < C ? pos[e] : p;
       pre_acc[k] = e < C && !tova ? acc[e] : 0.f;
     }
     // every head's maximum and row sum in one pass over the logits, two block reductions
     const float sl2 = D.scale_log2;
-    block_reduce_max_v<G>(mx, shf);   // its first barrier also publishes the logits in LDS
+    block_reduce_max_v<G, NW>(mx, shf);   // its first barrier also publishes the logits in LDS
     float sm[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       mx[g] *= sl2;
       sm[g] = 0.f;
     }
-    for (int e = tid; e <= C; e += kDecThreads) {
+    for (int e = tid; e <= C; e += NT) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float x = __builtin_amdgcn_exp2f(fmaf(sZ[g * (C + 1) + e], sl2, -mx[g]));
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
         sm[g] += x;
       }
     }
-    block_reduce_sum_v<G>(sm, shf);
+    block_reduce_sum_v<G, NW>(sm, shf);
     float inv[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) inv[g] = 1.0f / sm[g];
@@ -267,10 +266,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     };
 #pragma unroll
     for (int k = 0; k < kDecPre; ++k)
-      if (tid + kDecThreads * k <= C) visit(tid + kDecThreads * k, pre_acc[k], pre_pos[k]);
-    for (int e = tid + kDecThreads * kDecPre; e <= C; e += kDecThreads)
+      if (tid + NT * k <= C) visit(tid + NT * k, pre_acc[k], pre_pos[k]);
+    for (int e = tid + NT * kDecPre; e <= C; e += NT)
       visit(e, e < C && !tova ? acc[e] : 0.f, e < C ? pos[e] : p);
-    best = block_reduce_min_u64(best, shu);
+    best = block_reduce_min_u64<NW>(best, shu);
     const int vpos = (int)(uint32_t)(best & 0xffffffffu);
     // slot holding the winning position (positions are distinct); C = the new token
     __shared__ int sVictim;
@@ -279,8 +278,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     if (best != ~0ull) {
 #pragma unroll
       for (int k = 0; k < kDecPre; ++k)
-        if (tid + kDecThreads * k <= C && pre_pos[k] == vpos) sVictim = tid + kDecThreads * k;
-      for (int e = tid + kDecThreads * kDecPre; e <= C; e += kDecThreads) {
+        if (tid + NT * k <= C && pre_pos[k] == vpos) sVictim = tid + NT * k;
+      for (int e = tid + NT * kDecPre; e <= C; e += NT) {
         const int ps = e < C ? pos[e] : p;
         if (ps == vpos) sVictim = e;
       }
@@ -289,7 +288,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
     victim = sVictim;
     if (victim == C) victim = -1;
     if (!tova)
-      for (int e = tid; e < C; e += kDecThreads) acc[e] = (e == victim) ? sAcc[C] : sAcc[e];
+      for (int e = tid; e < C; e += NT) acc[e] = (e == victim) ? sAcc[C] : sAcc[e];
   }
   // the new token takes the victim's slot
   if (victim >= 0) {
@@ -304,32 +303,47 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(const DecodeLaunch 
   if (tid == 0 && ly.victim) ly.victim[bh] = victim;
 }
 
+template <int G, int NT>
+int launch_decode_kernel(const DecodeLaunch& D, unsigned grid, size_t lds, hipStream_t st) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<G, NT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    if (e != hipSuccess) return (int)e;
+    attr_set = true;
+  }
+  profile_mark(kStageDecode, false, st);
+  decode_kernel<G, NT><<<grid, NT, lds, st>>>(D);
+  profile_mark(kStageDecode, true, st);
+  return (int)hipGetLastError();
+}
+
+template <int G>
+int launch_decode_group(const DecodeLaunch& D, int max_capacity, hipStream_t st) {
+  const unsigned grid = (unsigned)(D.n_layers * D.batch * D.n_kv_heads);
+  const size_t lds = sizeof(float) * (size_t)(G + 1) * (max_capacity + 1);
+  // Twice the waves a workgroup, so twice the key rows in flight, where the workgroups leave a CU few of them:
+  // one workgroup per CU (256 of 512 entries: 16.0 -> 13.4 us, of 2048: 44 -> 31; below 128 entries a second
+  // block of rows is empty: 64: 7.1 -> 8.0), or at most five by their LDS with more of them waiting (4096 of
+  // 2048 entries: 383 -> 362, eight heads a group 729 -> 571).  Otherwise the smaller ones end more evenly (512
+  // of 512 entries: 19.7 against 20.8; 16384 of 1024: 716 against 726).  Four times the waves measured
+  // slower everywhere (256 of 512: 16.1, 16384 of 1024: 1233).
+  const size_t by_lds = 160 * 1024 / lds;
+  const bool wide = grid <= 256 ? max_capacity >= 128 : by_lds <= 5 && grid > 256 * by_lds;
+  return wide ? launch_decode_kernel<G, 512>(D, grid, lds, st) : launch_decode_kernel<G, 256>(D, grid, lds, st);
+}
+
 }  // namespace
 
 int launch_decode(const DecodeLaunch& D, int max_capacity, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const unsigned grid = (unsigned)(D.n_layers * D.batch * D.n_kv_heads);
-  const size_t lds = sizeof(float) * (size_t)(D.group + 1) * (max_capacity + 1);
-  static bool attr_set = false;
-  if (!attr_set) {
-    const void* fns[4] = {reinterpret_cast<const void*>(decode_kernel<1>), reinterpret_cast<const void*>(decode_kernel<2>),
-                          reinterpret_cast<const void*>(decode_kernel<4>), reinterpret_cast<const void*>(decode_kernel<8>)};
-    for (const void* f : fns) {
-      hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-      if (e != hipSuccess) return (int)e;
-    }
-    attr_set = true;
-  }
-  profile_mark(kStageDecode, false, stream);
   switch (D.group) {
-    case 1: decode_kernel<1><<<grid, kDecThreads, lds, st>>>(D); break;
-    case 2: decode_kernel<2><<<grid, kDecThreads, lds, st>>>(D); break;
-    case 4: decode_kernel<4><<<grid, kDecThreads, lds, st>>>(D); break;
-    case 8: decode_kernel<8><<<grid, kDecThreads, lds, st>>>(D); break;
+    case 1: return launch_decode_group<1>(D, max_capacity, st);
+    case 2: return launch_decode_group<2>(D, max_capacity, st);
+    case 4: return launch_decode_group<4>(D, max_capacity, st);
+    case 8: return launch_decode_group<8>(D, max_capacity, st);
     default: return (int)hipErrorInvalidValue;
   }
-  profile_mark(kStageDecode, true, stream);
-  return (int)hipGetLastError();
 }
 
 }  // namespace rkv
