@@ -792,30 +792,34 @@ __device__ __forceinline__ uint32_t rank_bits(float v) {
 //           group mean, Su the plain group mean, as the scoring kernels store them.
 // It is slow (two passes of scalar FMAs over the job) and only runs for flagged jobs; inlined,
 // with the query rows read from LDS, so the selection kernels need no stack.  Needs
-// G * w <= kRepairRows (256, every window-scored layout), blockDim >= kRepairRows and kRepairLds
-// bytes of LDS at `lds`.
+// G * w <= 256 (every window-scored layout), blockDim 256 or 1024 and repair_lds(G, w, blockDim) bytes of LDS
+// at `lds`.  That is sized by the layout: with 128 rows and four heads two selection workgroups of
+// 1024 threads fit a CU.
 // ---------------------------------------------------------------------------------------------
-constexpr int kRepairRows = kMaxRowTiles * 32;   // G * w of the window-scored layouts
-constexpr int kRepairKeyLanes = 4;               // blockDim / kRepairRows at most
-constexpr int kRepairLds = (kRepairRows * kHeadDim * 2) + 4 * (2 * kRepairRows + 2 * kRepairKeyLanes * kRepairRows + 8 * 1024);
-static_assert(kRepairLds <= kSelectLds, "the repair runs in the selection kernels' dynamic LDS");
+__host__ __device__ constexpr int repair_rows(int G, int w) { return G * w <= 128 ? 128 : kMaxRowTiles * 32; }
+// query rows; row maxima and sums; their partials (blockDim / rows key lanes); column sums of a chunk
+__host__ __device__ constexpr int repair_lds(int G, int w, int threads) {
+  return repair_rows(G, w) * kHeadDim * 2 + 4 * (2 * repair_rows(G, w) + 2 * threads + G * threads);
+}
+static_assert(repair_lds(8, 32, 1024) <= kSelectLds, "the repair runs in the selection kernels' dynamic LDS");
 
 __device__ __forceinline__ void rescore_exact(const uint16_t* qjob, const uint16_t* khead, float* S, float* Su, int L,
                                            int w, int G, int ph, int snap, float sl2, float* lds) {
   const int T = blockDim.x, tid = threadIdx.x;
   const int R = G * w;
-  uint32_t* sQ = reinterpret_cast<uint32_t*>(lds);   // [128][64] bf16 pairs of the job's query rows
-  float* sM = lds + kRepairRows * kHeadDim / 2;        // [128] row maxima (log2 units)
-  float* sR = sM + kRepairRows;                        // [128] reciprocal row sums
-  float* sPm = sR + kRepairRows;                       // [key lanes][128] partial maxima
-  float* sPs = sPm + kRepairKeyLanes * kRepairRows;    // [key lanes][128] partial sums
-  float* sA = sPs + kRepairKeyLanes * kRepairRows;     // [G][T] column sums of a chunk
+  const int RR = repair_rows(G, w);
+  uint32_t* sQ = reinterpret_cast<uint32_t*>(lds);   // [RR][64] bf16 pairs of the job's query rows
+  float* sM = lds + RR * kHeadDim / 2;        // [RR] row maxima (log2 units)
+  float* sR = sM + RR;                        // [RR] reciprocal row sums
+  float* sPm = sR + RR;                       // [key lanes][RR] partial maxima
+  float* sPs = sPm + T;                       // [key lanes][RR] partial sums
+  float* sA = sPs + T;                        // [G][T] column sums of a chunk
   const float NEG_INF = -__builtin_inff();
-  for (int e = tid; e < kRepairRows * kHeadDim / 2; e += T)
+  for (int e = tid; e < RR * kHeadDim / 2; e += T)
     sQ[e] = (e >> 6) < R ? reinterpret_cast<const uint32_t*>(qjob)[e] : 0u;
   __syncthreads();
   // ---- pass 1
-  const int nkl = T / kRepairRows, row = tid % kRepairRows, kl = tid / kRepairRows;
+  const int nkl = T / RR, row = tid % RR, kl = tid / RR;
   {
     float m = NEG_INF, sum = 0.f;
     if (row < R) {
@@ -842,14 +846,14 @@ __device__ __forceinline__ void rescore_exact(const uint16_t* qjob, const uint16
         }
       }
     }
-    sPm[kl * kRepairRows + row] = m;
-    sPs[kl * kRepairRows + row] = sum;
+    sPm[kl * RR + row] = m;
+    sPs[kl * RR + row] = sum;
   }
   __syncthreads();
-  if (tid < kRepairRows) {
+  if (tid < RR) {
     float m = NEG_INF, sum = 0.f;
     for (int k = 0; k < nkl; ++k) {
-      const float pm = sPm[k * kRepairRows + tid], ps = sPs[k * kRepairRows + tid];
+      const float pm = sPm[k * RR + tid], ps = sPs[k * RR + tid];
       if (!(ps > 0.f)) continue;
       if (!(sum > 0.f)) {
         m = pm;
@@ -1103,7 +1107,9 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const PrefillLaunch P)
 // threads: prompts of up to 8K, 16K or 32K keys):
 // wave wv owns the contiguous key range [w0, w1); its lane l holds keys w0 + 64 i + l.  Dynamic
 // LDS holds the job's slice-edge column sums and the repaired scores next to slice borders
-// (with their per-head pool maxima).
+// (with their per-head pool maxima).  Bound by the latency of its passes between barriers, so two workgroups
+// should share a CU: at 8 scores a thread the registers are held to 64 and the LDS to what the layout's
+// rescoring needs (1920 jobs of 8192 keys: 92 -> 71 us; at 16 scores that would spill).
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 static_assert(kSelWaves <= 16, "wave prefixes are summed over one 16-lane DPP row");
@@ -1111,7 +1117,7 @@ constexpr int kSelRegsMax = 32;                              // scores per threa
 constexpr int kSelRegsMaxKeys = kSelRegsMax * kSelThreads;   // 32K keys
 
 template <int kSelRegs>
-__global__ __launch_bounds__(kSelThreads) void select_regs_kernel(const PrefillLaunch P) {
+__global__ __launch_bounds__(kSelThreads, kSelRegs == 8 ? 8 : 4) void select_regs_kernel(const PrefillLaunch P) {
   // dynamic LDS: [n_edge] edges, [n_fix] repaired scores (or the exact rescoring's staging)
   extern __shared__ __attribute__((aligned(16))) float sDyn[];
   __shared__ int sHist[2][kHistBins];   // pass p uses buffer p % 2
@@ -1565,7 +1571,7 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
                                         (size_t)(P.n_slices > 0 ? P.n_slices - 1 : 0) * 2 * P.pool_half *
                                             (1 + P.group));
     if (P.seq_len <= kSelRegsMaxKeys && dyn <= (size_t)kSelectLds - 2 * kHistBins * 4 - 256) {
-      const size_t lds = std::max(dyn, (size_t)kRepairLds);
+      const size_t lds = std::max(dyn, P.n_window > 0 ? (size_t)repair_lds(P.group, P.window, kSelThreads) : (size_t)0);
       if (P.seq_len <= 8 * kSelThreads)
         launch_staged(kStageSelect, select_regs_kernel<8>, dim3(n_sel), dim3(kSelThreads), lds, st, P);
       else if (P.seq_len <= 16 * kSelThreads)
