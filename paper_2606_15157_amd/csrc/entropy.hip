@@ -8,6 +8,9 @@
 // pass of causal_rows.h over 128 or 256 query rows of the group.  Per row it takes Z = sum e and
 // T = sum e x over the row's keys, e = exp2(x), and
 //   H = -sum p ln p = ln 2 (log2 Z - T / Z).
+// Bound: 20 cycles of VALU issue per 64 logits beside 16 of the matrix pipe.  256 jobs of 4096 queries and four
+// heads: 2.3 ms (3.4 with 16x16x32 MFMA, 32 rows a wave), 2.2 TFLOP of causal logits; the last 515 queries of
+// 9001, 128 jobs of two heads: 0.37 ms (0.70).
 // A non-finite row is written as it is and reported by the averaging kernel.
 // Each workgroup also leaves the double-precision sum of its rows; entropy_mean_kernel (one
 // workgroup per layer) adds those in a fixed order.

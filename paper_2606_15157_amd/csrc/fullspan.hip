@@ -13,6 +13,10 @@
 //   the same rows, which stay in their XCD's L2 cache).  The keys are the A operand, so a lane holds one
 //   query row, with its normaliser in one register, and sixteen keys of each block: it sums
 //   p = exp2(x - Lambda_t) per key in 32 registers, and the 32 lanes of a key meet once at the end.
+// Bound: issue of the exponentials and MFMAs, each logit twice.  32 jobs of 8192 queries and four heads: rows
+// 1.04 ms (1.56 with 16x16x32 MFMA, 32 rows a wave and 128-key tiles through registers), columns 0.95 (2.05),
+// 1.1 TFLOP of causal logits each; the error of the scores against 64 bits 1.7e-7 (8e-6, in columns summed
+// over thousands of terms a lane).
 // Jobs here are the full-span ones: job = (slot * B + b) * Hkv + h with slot >= n_window.
 #include <hip/hip_runtime.h>
 
