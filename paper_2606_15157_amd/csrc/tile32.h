@@ -130,6 +130,9 @@ __device__ __forceinline__ void load_block(const uint16_t* row, bf16x8 (&f)[8]) 
     f[st] = __builtin_bit_cast(bf16x8, v);
   }
 }
+// The two bf16 in a dword, which is taken by value: __builtin_bit_cast of a vector's element reads element 0
+// whatever the index (seen with the compiler of ROCm 7.2).
+__device__ __forceinline__ bf16x2 bf16_pair(uint32_t v) { return __builtin_bit_cast(bf16x2, v); }
 // Dot product of this lane's row (in f) with another row in memory, both halves of the row summed.
 __device__ __forceinline__ float block_dot(const bf16x8 (&f)[8], const uint16_t* row) {
   const int hf = (threadIdx.x >> 5) & 1;
@@ -139,8 +142,7 @@ __device__ __forceinline__ float block_dot(const bf16x8 (&f)[8], const uint16_t*
     const u32x4 x = *reinterpret_cast<const u32x4*>(row + 8 * (2 * st + hf));
     const u32x4 y = __builtin_bit_cast(u32x4, f[st]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x[u]), __builtin_bit_cast(bf16x2, y[u]), a, false);
+    for (int u = 0; u < 4; ++u) a = __builtin_amdgcn_fdot2_f32_bf16(bf16_pair(x[u]), bf16_pair(y[u]), a, false);
   }
   const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
@@ -207,8 +209,7 @@ __device__ __forceinline__ float block_dot16(const bf16x8 (&f)[4], const uint16_
     const u32x4 x = *reinterpret_cast<const u32x4*>(row + 8 * (4 * st + lg));
     const u32x4 y = __builtin_bit_cast(u32x4, f[st]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x[u]), __builtin_bit_cast(bf16x2, y[u]), a, false);
+    for (int u = 0; u < 4; ++u) a = __builtin_amdgcn_fdot2_f32_bf16(bf16_pair(x[u]), bf16_pair(y[u]), a, false);
   }
   a += __shfl_xor(a, 16);
   return a + __shfl_xor(a, 32);
