@@ -214,9 +214,10 @@ __device__ __forceinline__ float block_dot16(const bf16x8 (&f)[4], const uint16_
   a += __shfl_xor(a, 16);
   return a + __shfl_xor(a, 32);
 }
+// Accumulators of block b start as start[b].
 template <bool kStreamA, typename Value>
 __device__ __forceinline__ void tile_step16(const uint16_t* tile, uint32_t tl, int sub, const bf16x8 (&own)[4][4],
-                                            f32x4 (&acc)[2][4], Value&& value) {
+                                            const f32x4 (&start)[4], f32x4 (&acc)[2][4], Value&& value) {
   auto frag = [&](int j) __attribute__((always_inline)) {   // (kh, st) = (j / 4, j % 4)
     return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(tile) + (tl ^ (64u * (j & 3))) + 4096u * (j >> 2) + 8192u * sub);
   };
@@ -231,7 +232,7 @@ __device__ __forceinline__ void tile_step16(const uint16_t* tile, uint32_t tl, i
     if (j + 2 < 8) f[(j + 2) % 3] = frag(j + 2);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f}, c = (j & 3) == 0 ? z : acc[j >> 2][b];
+      const f32x4 c = (j & 3) == 0 ? start[b] : acc[j >> 2][b];
       acc[j >> 2][b] = kStreamA ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j % 3], own[b][j & 3], c, 0, 0, 0)
                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(own[b][j & 3], f[j % 3], c, 0, 0, 0);
     }

@@ -113,17 +113,18 @@ struct WideSums {
   // the wave's row sums, over the lanes of a row, to out[0 .. 63]
   __device__ __forceinline__ void put(double* out) const { out[threadIdx.x & 63] = halves_sum(Z); }
 };
-// FineSums, 16x16x32 MFMA: the same, with half as many roundings of z (see FineRows).
+// FineSums, 16x16x32 MFMA: half as many roundings of z, and accumulators that start from -c (see FineRows).
 struct FineSums {
   static constexpr int kBlocks = 4, kRows = 16;
   f32x4 acc[2][2][4];
   bf16x8 q[4][4];
   int last[4];
-  float nc[4], zs[4][4], Zr[4], sl2;
+  f32x4 nc[4];        // -c in every element
+  float zs[4][4], Zr[4], sl2;
   double Z[4];
   __device__ __forceinline__ void load(int b, const uint16_t* row) { load_block16(row, q[b]); }
   __device__ __forceinline__ float dot(int b, const uint16_t* key) const { return block_dot16(q[b], key); }
-  __device__ __forceinline__ void reference(int b, float c) { nc[b] = -c * sl2; }
+  __device__ __forceinline__ void reference(int b, float c) { nc[b] = {-c, -c, -c, -c}; }
   template <int X>
   __device__ __forceinline__ void hide() {
 #pragma unroll
@@ -132,13 +133,13 @@ struct FineSums {
   template <int X>
   __device__ __forceinline__ void exps(int u) {
     const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
-    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][kh][b][i], sl2, nc[b]));
+    const float e = __builtin_amdgcn_exp2f(acc[X][kh][b][i] * sl2);
     if (kh == 0) zs[b][i] = e;
     else zs[b][i] += e;
   }
   template <int X>
   __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
-    tile_step16<true>(tile, tile_lane16(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+    tile_step16<true>(tile, tile_lane16(), sub, q, nc, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
   }
   template <int X>
   __device__ __forceinline__ void mask(int k0) {
@@ -323,18 +324,20 @@ struct WideRows {
     }
   }
 };
-// FineRows, 16x16x32 MFMA: p = exp2(x) w_r, x = z_rj log2(e)/sqrt(d) - c_r log2(e)/sqrt(d), with the weight
-// w_r = 1 / z_r, so that no number of the size of Lambda is rounded, and a logit is rounded half as often:
-// the accuracy of the pipelined kernel for about 4 % more time (batch 3, L = 3331, w = 27, two heads a group:
-// error 1.54e-7 -> 1.37e-7 and a call 93 -> 97 us; the pipelined kernel 1.25e-7 and 113 us).
+// FineRows, 16x16x32 MFMA: p = exp2(x) w_r, x = (z_rj - c_r) log2(e)/sqrt(d) from accumulators that start from
+// -c_r, with the weight w_r = 1 / z_r.  That is the pipelined kernel's arithmetic: no number of the size of
+// Lambda is rounded, a logit is rounded half as often, and near the reference, where the large probabilities
+// are, against a small number.  Its error is the pipelined kernel's: 1.00 of it over 22 padded and short layouts
+// of 16 prompts each (0.97 to 1.03 a layout; batch 3, L = 3331, w = 27, two heads a group: 1.20e-7 and 1.21e-7).
+// Accumulators from 0 left 1.04 to 1.15 of it, and WideRows 1.54e-7 there for 4 % less time.
 struct FineRows {
   f32x4 acc[2][2][4];
   bf16x8 q[4][4];
-  f32x4 nc[4], wt[4];   // -c log2(e)/sqrt(d), w
+  f32x4 nc[4], wt[4];   // -c, w
   float cs[2][2];       // column sums of a key half and row tile
   float sl2;
-  static __device__ __forceinline__ float2 numbers(float c, float z, float sl2) {
-    return {-c * sl2, c < __builtin_inff() ? 1.f / z : 0.f};
+  static __device__ __forceinline__ float2 numbers(float c, float z, float) {
+    return {-c, c < __builtin_inff() ? 1.f / z : 0.f};
   }
   template <typename Row>
   __device__ __forceinline__ void load(Row&& row) {
@@ -356,13 +359,13 @@ struct FineRows {
   template <int X>
   __device__ __forceinline__ void exps(int u) {
     const int kh = u >> 4, b = (u >> 2) & 3, i = u & 3;
-    const float e = __builtin_amdgcn_exp2f(fmaf(acc[X][kh][b][i], sl2, nc[b][i]));
+    const float e = __builtin_amdgcn_exp2f(acc[X][kh][b][i] * sl2);
     if ((u & 7) == 0) cs[kh][b >> 1] = e * wt[b][i];
     else cs[kh][b >> 1] = fmaf(e, wt[b][i], cs[kh][b >> 1]);
   }
   template <int X>
   __device__ __forceinline__ void step(const uint16_t* tile, int sub) {
-    tile_step16<false>(tile, tile_lane16(), sub, q, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
+    tile_step16<false>(tile, tile_lane16(), sub, q, nc, acc[X], [&](int u) __attribute__((always_inline)) { exps<1 - X>(u); });
   }
   template <int X, typename Seen>
   __device__ __forceinline__ void mask(Seen&& seen) {
@@ -435,12 +438,13 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
   Rows rows;
   rows.sl2 = sl2;
   if (tid < R) {
-    float z;   // the row's sum (several parts: theirs added in part order)
+    float z;   // the row's sum (several parts: theirs added in part order, rounded once)
     if (P.window_parts == 1) {
       z = P.lam[(size_t)job * R + tid];
     } else {
-      z = 0.f;
-      for (int p = 0; p < P.window_parts; ++p) z += P.stats[((size_t)job * P.window_parts + p) * R + tid];
+      double zd = 0.0;
+      for (int p = 0; p < P.window_parts; ++p) zd += (double)P.stats[((size_t)job * P.window_parts + p) * R + tid];
+      z = (float)zd;
     }
     // padding and overflowing rows: reference +inf, every probability 0
     float c = P.ncl[(size_t)job * R + tid];
@@ -472,21 +476,29 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
     if (per_head == 1 && cbase + kSlice <= npre && (!snap || ph == 3)) {
       const int t2 = tid ^ (sb << 7);   // the wave pairs take turns
       if (t2 < kSlice) {
+        // head pairs: two roundings of a mean of four, where one head after another takes three
         const float* c = &col[0][kPad + t2];
+        auto pool = [](const float* x) __attribute__((always_inline)) {
+          const uint32_t* u = reinterpret_cast<const uint32_t*>(x);
+          return __uint_as_float(max(max(max(u[-3], u[-2]), max(u[-1], u[0])), max(max(u[1], u[2]), u[3])));
+        };
         float su = 0.f, sc = 0.f;
         if (snap) {
-#pragma unroll 4
-          for (int g = 0; g < G; ++g, c += kColRow) {
-            const uint32_t* u = reinterpret_cast<const uint32_t*>(c);
-            const uint32_t m = max(max(max(u[-3], u[-2]), max(u[-1], u[0])), max(max(u[1], u[2]), u[3]));
+#pragma unroll 2
+          for (int g = 0; g + 1 < G; g += 2, c += 2 * kColRow) {
+            su += c[0] + c[kColRow];
+            sc += pool(c) + pool(c + kColRow);
+          }
+          if (G & 1) {
             su += c[0];
-            sc += __uint_as_float(m);
+            sc += pool(c);
           }
           Srow[t2] = sc * inv_g;
           if (P.want_unpooled) P.Su[(size_t)job * L + cbase + t2] = su * inv_g;
         } else {
-#pragma unroll 4
-          for (int g = 0; g < G; ++g, c += kColRow) su += c[0];
+#pragma unroll 2
+          for (int g = 0; g + 1 < G; g += 2, c += 2 * kColRow) su += c[0] + c[kColRow];
+          if (G & 1) su += c[0];
           Srow[t2] = su * inv_g;
         }
       } else if (snap && t2 - kSlice < 12 * G) {   // offsets 0 .. 5 and 122 .. 127 of every head

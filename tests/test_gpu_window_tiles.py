@@ -43,3 +43,33 @@ def test_many_jobs_take_the_window_kernels(L, w, hq, hkv):
     rules = [OP.SNAPKV, OP.H2O] * 8
     layers = [[gen(32, 0, l, L, w=w, Hq=hq, Hkv=hkv)] for l in range(16)]
     run_case(rules, [60] * 16, layers, window=w, label=f"many_L{L}_w{w}")
+
+
+@pytest.mark.parametrize("L,w,hq,hkv", [(3331, 27, 16, 8), (1024, 32, 32, 8)], ids=["padded", "few_slices"])
+def test_window_kernels_are_as_exact_as_the_pipelined_one(L, w, hq, hkv):
+    """The same layers in one call (128 jobs: the window kernels) and one by one (8 jobs: the pipelined kernel),
+    against 64 bits: the first is no further off.  Both errors are means over 128 jobs of about 1e-7 each,
+    so their ratio is known to about 2 %."""
+    import paper_2606_15157_amd as rkv
+    import torch
+    from parity import bits_to_torch
+    from test_gpu_causal_tiles import attention
+    x = [gen(33, 0, l, L, w=w, Hq=hq, Hkv=hkv) for l in range(16)]
+    q, k = ([bits_to_torch(y[n][None]) for y in x] for n in ("q", "k"))
+
+    def scores(at):
+        plan = rkv.Plan([rkv.SNAPKV] * len(at), [w + 100] * len(at), window=w, pool_kernel=7)
+        out = rkv.evict_prefill(plan, [q[l] for l in at], [k[l] for l in at], [k[l] for l in at], score_out=True)
+        return torch.cat(out["scores"])[..., :L - w].double()
+
+    def pooled(a, b):
+        sums = attention(a, b).sum(3)[..., :L - w]
+        return torch.nn.functional.max_pool1d(sums.flatten(0, 2), 7, 1, 3).view(sums.shape).mean(2)
+
+    want = torch.cat([pooled(a, b) for a, b in zip(q, k)])
+
+    def error(got):
+        return ((got - want).norm(dim=-1) / want.norm(dim=-1)).mean().item()
+
+    window, pipelined = error(scores(range(16))), error(torch.cat([scores([l]) for l in range(16)]))
+    assert window < 2e-7 and window <= 1.04 * pipelined, (window, pipelined)
