@@ -63,8 +63,7 @@ struct PrefillLaunch {
   int32_t window_parts;   // window rows kernel: workgroups (key ranges) per job
   int32_t window_ranges;  // window columns kernel: likewise
   // workspace regions
-  uint32_t* counters;     // [0] status; job j's line at [kCounterStride * (1 + j)]: word 1 its repair flag,
-                          // from word 2 the overflow marks of the window rows kernel's parts
+  uint32_t* counters;     // [0] status; job j's line at [kCounterStride * (1 + j)]: word 1 its repair flag
   float* stats;           // [J][n_slices][128]  pipelined kernel: per-slice row sums (NaN until stored);
                           // [J][window_parts][R]  window kernels with several parts: partial row sums
   float* part;            // [J][kPipeGroups][128]  pipelined kernel: per-group sums of those (NaN until stored)

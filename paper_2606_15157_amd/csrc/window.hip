@@ -15,9 +15,7 @@
 //   the columns kernel then adds the parts' row sums).  The keys are the A operand, so a lane holds
 //   one window row of each block and some keys, and the row's sum and reference are one register each: e =
 //   exp2((z - c_r) log2(e) / sqrt(d)) against a fixed per-row reference c_r = max(logit with the
-//   row's own key, logit with key 0).  c_r and the row sum go to the workspace; a row whose sum overflows (a
-//   key more than ~88 natural-log units above its reference) marks the part, and the columns kernel
-//   flags the job for the exact rescoring of the selection kernels.
+//   row's own key, logit with key 0).  c_r and the row sum go to the workspace.
 // window_cols_kernel<NRT>: one workgroup per (job, range of 128-key slices).  The window rows are
 //   the A operand, so a lane holds one key and some rows of each block, with two numbers of each row in
 //   registers; its probabilities are summed over a block's rows in registers and
@@ -44,8 +42,6 @@
 
 namespace rkv {
 namespace {
-
-constexpr int kPartMark = 2;   // words of a job's counter line from which its parts' overflow marks sit
 
 // Window row r of a job: query head g = r / tpr and window index ii = r % tpr (tpr = rows per
 // head in the padded layout); valid when g < G and ii < w.
@@ -246,24 +242,16 @@ __global__ __launch_bounds__(256, 2) void window_rows_kernel(const PrefillLaunch
   turn();
   rows.put(&sZ[kg][64 * rg]);
   tile_barrier();
-  bool over = false;
   if (tid < R) {
-    const WinRow x = win_row(tid, tpr, G, w);
     double zd = sZ[0][tid];
 #pragma unroll
     for (int k = 1; k < KG; ++k) zd += sZ[k][tid];
     const float z = (float)zd;
-    over = x.valid && !(z < __builtin_inff());   // a key far above the row's reference
-    if (part == 0) P.ncl[(size_t)job * R + tid] = x.valid ? sC[tid] : __builtin_inff();
+    if (part == 0) P.ncl[(size_t)job * R + tid] = win_row(tid, tpr, G, w).valid ? sC[tid] : __builtin_inff();
     if (parts == 1) P.lam[(size_t)job * R + tid] = z;
     else P.stats[((size_t)job * parts + part) * R + tid] = z;
   }
-  // The part's overflow mark, for the columns kernel; it also starts the call's status word.
-  const int any = __syncthreads_or(over);
-  if (tid == 0) {
-    P.counters[(size_t)kCounterStride * (1 + job) + kPartMark + part] = any ? 1u : 0u;
-    if (blockIdx.x == 0 && P.first_group) P.counters[0] = 0u;
-  }
+  if (blockIdx.x == 0 && tid == 0 && P.first_group) P.counters[0] = 0u;   // the call's status word
 }
 
 // How the columns kernel takes a wave's 64 window rows: they are the A operand, so a lane holds one key and some
@@ -421,14 +409,6 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
   const uint16_t* qjob = ly.q + (size_t)(s * Hq + h * G) * w * kHeadDim;
   const float sl2 = P.scale_log2, inv_g = 1.f / (float)G;
   const int npre = L - w, ph = P.pool_half;
-  if (range == 0 && tid == 0) {
-    // a job with an overflowing row is rescored exactly before selection
-    uint32_t* line = P.counters + (size_t)kCounterStride * (1 + job);
-    uint32_t any = 0u;
-    for (int p = 0; p < P.window_parts; ++p) any |= line[kPartMark + p];
-    line[1] = any;
-    if (any) atomicOr(P.counters, RKV_STATUS_REPAIRED);
-  }
   if (n <= 0) return;
 
   if (tid < 2 * NRT * 2 * kPad) {
@@ -437,6 +417,7 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
   }
   Rows rows;
   rows.sl2 = sl2;
+  bool over = false;
   if (tid < R) {
     float z;   // the row's sum (several parts: theirs added in part order, rounded once)
     if (P.window_parts == 1) {
@@ -449,12 +430,21 @@ __global__ __launch_bounds__(256, 2) void window_cols_kernel(const PrefillLaunch
     // padding and overflowing rows: reference +inf, every probability 0
     float c = P.ncl[(size_t)job * R + tid];
     if (!(z < __builtin_inff())) {
+      over = win_row(tid, tpr, G, w).valid;
       z = 1.f;
       c = __builtin_inff();
     }
     const float2 n = Rows::numbers(c, z, sl2);
     sA[tid] = n.x;
     sB[tid] = n.y;
+  }
+  if (range == 0) {
+    // A row whose sum overflows, in one part or over all of them: the job is rescored exactly before selection.
+    const int any = __syncthreads_or(over);
+    if (tid == 0) {
+      P.counters[(size_t)kCounterStride * (1 + job) + 1] = any ? 1u : 0u;
+      if (any) atomicOr(P.counters, RKV_STATUS_REPAIRED);
+    }
   }
   rows.load([&](int r) __attribute__((always_inline)) {
     const WinRow x = win_row(64 * rg + r, tpr, G, w);
