@@ -1487,8 +1487,12 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
   // every slice of a job fits in the resident workgroups; other layouts take the window kernels
   // (window.hip), which the test hook RKV_FORCE_WINDOW=1 selects everywhere
   static const int pipe_wg = resident_pipe_groups();
+  // and so do queries or keys that are not 16-byte aligned (views into larger buffers): the pipelined kernel
+  // brings both in by LDS DMA of 16 bytes a lane, the window kernels read such rows through registers
+  uintptr_t at = 0;
+  for (int s = 0; s < P.n_window; ++s) at |= reinterpret_cast<uintptr_t>(P.layer[s].q) | reinterpret_cast<uintptr_t>(P.layer[s].k);
   const bool pipe_fits = n_jobs > 0 && row_tiles == 4 && P.force_window == 0 && P.n_slices <= kPipeMaxSlices &&
-                         P.n_slices <= pipe_wg;
+                         P.n_slices <= pipe_wg && at % 16 == 0;
   // Of those, the window kernels are the faster ones once the chip is full and either
   //   - rows are padded (fewer than 128, or a window that is no multiple of 32): the pipelined
   //     kernel then masks every tile (30 layers at L = 4096, two query heads per KV head: 163 us

@@ -59,13 +59,15 @@ __device__ __forceinline__ void issue_tile(const uint16_t* rows, int row0, int n
     dma16s_pair(base, off, lds + 1024u * wv);
     dma16s_pair(base + 8192, off, lds + 1024u * wv + 8192u);
   } else if (!aligned) {
-#pragma unroll 1
+    u32x4 v[kTileDma];
+#pragma unroll
     for (int u = 0; u < kTileDma; ++u) {
       const int row = min(row0 + 16 * u + r4, n - 1);
-      u32x4 v;
-      __builtin_memcpy(&v, reinterpret_cast<const char*>(rows + (size_t)row * kHeadDim) + chunk, 16);
-      *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(lds + 1024u * (wv + 4 * u) + 16u * lane) = v;
+      __builtin_memcpy(&v[u], reinterpret_cast<const char*>(rows + (size_t)row * kHeadDim) + chunk, 16);
     }
+#pragma unroll
+    for (int u = 0; u < kTileDma; ++u)
+      *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(lds + 1024u * (wv + 4 * u) + 16u * lane) = v[u];
     wait_vmcnt<0>();
   } else {
 #pragma unroll

@@ -110,6 +110,23 @@ def test_unaligned_window_inputs(monkeypatch):
     assert torch.equal(a["scores"][0], b["scores"][0]) and torch.equal(a["idx"][0], b["idx"][0])
 
 
+@pytest.mark.parametrize("which", ["queries", "keys"])
+def test_unaligned_inputs_do_not_take_the_pipelined_kernel(which, monkeypatch):
+    """One job of a short prompt, the pipelined kernel's, whose queries or keys are not 16-byte aligned: the
+    window kernels' bits."""
+    import paper_2606_15157_amd as rkv
+    import torch
+    L = 709
+    q, k, v = gen(47, 1, 8, 32, 128), gen(48, 1, 2, L, 128), gen(49, 1, 2, L, 128)
+    plan = rkv.Plan([rkv.SNAPKV, rkv.H2O], [200] * 2, window=32, pool_kernel=7)
+    x, y = (shifted(q), k) if which == "queries" else (q, shifted(k))
+    a = rkv.evict_prefill(plan, [q, x], [k, y], [v, v], score_out=True)   # the second layer's
+    monkeypatch.setenv("RKV_FORCE_WINDOW", "1")
+    b = rkv.evict_prefill(plan, [q, q], [k, k], [v, v], score_out=True)
+    for l in range(2):
+        assert torch.equal(a["scores"][l], b["scores"][l]) and torch.equal(a["idx"][l], b["idx"][l])
+
+
 def test_full_span_row_that_is_not_a_number():
     """Query 100 of head 0 is NaN: keys up to 100 of its KV head get no score, the keys after it theirs."""
     import torch
