@@ -52,8 +52,11 @@ FULL = [
     # L, B, Hq, Hkv
     (1, 1, 4, 1), (31, 1, 4, 1), (64, 1, 2, 2), (65, 2, 4, 2), (127, 1, 8, 1), (193, 1, 8, 2), (256, 1, 16, 2),
     (257, 1, 1, 1), (321, 2, 2, 1), (640, 1, 8, 2),
-    (129, 8, 32, 8), (300, 5, 32, 16),      # 64 and 160 jobs: two key groups
-    (259, 48, 8, 8), (300, 64, 16, 8),      # 384 and 512 jobs: one key group; four and eight row tiles
+    (129, 8, 32, 8),                        # 64 blocks of 256 keys: four key groups
+    (129, 9, 32, 8), (300, 5, 32, 16), (200, 20, 32, 4),      # 72, 160 and 80: two
+    (259, 48, 8, 8), (300, 64, 16, 8),      # 768 and 1024: one; four and eight row tiles
+    (259, 48, 32, 8), (259, 96, 32, 4),     # 768: one, four and eight heads per group
+    (700, 125, 12, 3),                      # 4125 blocks of query rows: job by job, 375 jobs in rounds of eight
 ]
 
 
@@ -71,6 +74,7 @@ ENTROPY = [
     (1, 1, 1, 4, 1), (64, 33, 1, 4, 1), (65, 65, 2, 2, 2), (127, 1, 1, 8, 1), (320, 129, 1, 4, 2), (513, 31, 1, 8, 2),
     (700, 257, 1, 1, 1), (641, 64, 1, 16, 2),
     (300, 300, 64, 16, 8), (260, 129, 128, 32, 8),   # eight row tiles, two and four heads per group
+    (260, 129, 43, 12, 3),                           # the last half of the queries: job by job, 129 jobs
 ]
 
 
