@@ -153,12 +153,12 @@ def test_odd_window_and_group_shapes():
     run_case(rules, [150, 150], layers, window=20, pool_kernel=5, label="w20g2")
 
 
-@pytest.mark.parametrize("w,Hq,Hkv", [(64, 16, 8), (100, 8, 8)], ids=["w64_g2", "w100_g1"])
+@pytest.mark.parametrize("w,Hq,Hkv", [(64, 16, 8), (100, 8, 8), (128, 8, 8)], ids=["w64_g2", "w100_g1", "w128_g1"])
 def test_wide_windows_few_heads(w, Hq, Hkv):
-    """Windows of two and four 32-row tiles per head with two and one query heads per KV head
-    (four row tiles in all: the pipelined kernel's two- and four-tile forms, the second with
-    padding rows), L = 5000 and four layers: more than four items per workgroup, so the
-    long-run form of the kernel."""
+    """Windows of two and four 32-row tiles per head with two and one query heads per KV head (four row
+    tiles in all), L = 5000 and four layers: 1280 items, more than four per workgroup.  Windows of 64 and 128
+    take the long-run form of the pipelined kernel's two- and four-tile forms; the padded rows of a window of
+    100 take the window kernels (from 1024 items)."""
     L = 5000
     rules = [OP.SNAPKV, OP.H2O, OP.SNAPKV, OP.H2O]
     layers = [[gen(13, 0, l, L, w=w, Hq=Hq, Hkv=Hkv)] for l in range(4)]
@@ -187,7 +187,7 @@ def test_long_prompts_general_selection(L, Hq, Hkv):
 
 @pytest.mark.parametrize("Hq,Hkv", [(8, 8), (32, 4)], ids=["g1", "g8"])
 def test_group_sizes_one_and_eight(Hq, Hkv):
-    """G = 1 (one row tile of 32, padded to four in the pipelined kernel) and G = 8 (eight row
+    """G = 1 (one row tile of 32, padded to four in the pipelined kernel: 32 jobs of 9 slices) and G = 8 (eight row
     tiles, the other scoring kernel), SnapKV and H2O, ragged L."""
     L = 1100
     rules = [OP.SNAPKV, OP.H2O]
@@ -226,9 +226,8 @@ def test_repeat_runs_are_bitwise_identical():
 
 
 def test_window_kernels_match_oracle_on_short_prompts(monkeypatch):
-    """The window scoring kernels (row normalisers, then column sums: prompts of more than 64
-    slices, eight row tiles), forced through the test hook on layouts the pipelined kernel would
-    otherwise take: the 1K case and a ragged length."""
+    """The window scoring kernels (row sums, then column sums), forced through the test hook on layouts
+    the pipelined kernel would otherwise take: the 1K case and a ragged length."""
     monkeypatch.setenv("RKV_FORCE_WINDOW", "1")
     run_case([OP.SNAPKV, OP.H2O], [128, 128], [[gen(1, 0, 0, 1024)], [gen(1, 0, 1, 1024)]], window=32,
              label="win_1k")
@@ -239,7 +238,7 @@ def test_window_kernels_match_oracle_on_short_prompts(monkeypatch):
 @pytest.mark.parametrize("L", [4096, 3000])
 def test_window_kernels_split_keys(monkeypatch, L):
     """Few jobs (two layers x 8 KV heads): the rows kernel splits each job's keys over several
-    workgroups (4 parts at L = 4096; 3 at L = 3000, the last with the ragged tail) and the columns
+    workgroups (5 parts at L = 4096; 4 at L = 3000, the last with the ragged tail) and the columns
     kernel adds their row sums."""
     monkeypatch.setenv("RKV_FORCE_WINDOW", "1")
     run_case([OP.SNAPKV, OP.H2O], [300, 300], [[gen(15, 0, 0, L)], [gen(15, 0, 1, L)]], window=32,
@@ -278,11 +277,15 @@ def test_reference_overflow_is_repaired_at_eight_row_tiles():
     run_case([OP.SNAPKV, OP.H2O], [200, 200], [[y], [y]], window=64, label="ref_overflow_w64", status=4)
 
 
-def test_status_word_spans_every_launch_group():
+@pytest.mark.parametrize("L,force", [(1024, "0"), (2100, "0"), (1024, "1")],
+                         ids=["window_pipelined", "pipelined_pipelined", "window_window"])
+def test_status_word_spans_every_launch_group(L, force, monkeypatch):
     """33 layers take two launch groups.  The overflow planted in layer 0 (first group) must still
     be visible in the status word after the second group ran, and both groups' layers (0, the
-    repaired one, and 32) match the oracle."""
-    L = 1024
+    repaired one, and 32) match the oracle.  The first group's 256 jobs take the window kernels at 8 slices,
+    the pipelined kernel at 17; the second group's 8 the pipelined kernel; the test hook takes the window
+    kernels for both."""
+    monkeypatch.setenv("RKV_FORCE_WINDOW", force)
     y = overflow_input(L)
     layers = [[y]] + [[gen(14, 0, l, L)] for l in range(1, 33)]
     run_case([OP.SNAPKV] * 33, [128] * 33, layers, window=32, label="two_groups", status=4)
