@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kPipeThreads, 1) void score_pipe_kernel(const Prefi
   const float sl2 = P.scale_log2;
   const float inv_g = 1.f / (float)G;
   uint32_t* status = P.counters;
-  // Only short runs have padded rows (longer ones take the window kernels).  The long-run form keeps their code
+  // Only short runs have padded rows (window_faster).  The long-run form keeps their code
   // all the same: without it its registers are dealt differently and the 32-layer route at 8K takes 207.0 us
   // against 206.0, at batch 8 1458 against 1444.
   const bool padded_rows = (G * NTH < 4) || (w != NTH * 32);
@@ -1478,6 +1478,26 @@ void launch_staged(int stage, void (*kernel)(KArgs...), dim3 grid, dim3 block, s
     hipLaunchKernelGGL(kernel, grid, block, shmem, st, args...);
 }
 
+// Whether the window kernels are the faster ones for a call that the pipelined kernel could take.  Times are of
+// a call, pipelined / window, on 256 workgroups.
+//   Padded rows (fewer than 128, or a window that is no multiple of 32): the pipelined kernel masks every tile.
+//   With 128 jobs 1.01 to 1.5 of the window kernels' time whatever the length, and with fewer from its long-run
+//   form on: 16 jobs of 64 slices (its last short run) 43 us / 47, 32 of 32 44 / 44, 24 of 48 50 / 46, 80 of
+//   13 1.04, 32 of 64 63 / 53.
+//   Otherwise: its two-level exchange is a large share of an item where a job has few slices, and every pass
+//   over the workgroups ends with a whole job where their count is a multiple of the slices: the same ones then
+//   always take a group's sums (240 jobs of 7, 8, 9 slices: 1.18, 1.29, 1.06; 16 slices 1.03 to 1.19 from 128
+//   jobs on, 17 slices 0.84 to 1.01).  The window kernels have 512 workgroups resident and fill them evenly up to as
+//   many jobs.  The most slices at which they are not the slower ones, and the ratio there and one further:
+//   128 jobs 5 (1.04, 0.94), 152 11 (1.02, 0.98), 192 10 (1.02, 0.97), 240 to 512 16 (1.18, 0.94), 576 6 (1.02,
+//   0.91) and 8 (1.12), 640 to 1536 8 (1.15, 0.94).
+bool window_faster(int n_jobs, int n_slices, bool padded, int pipe_wg) {
+  if (padded) return n_jobs >= 128 || (int64_t)n_jobs * n_slices > (int64_t)kPipeShortItems * pipe_wg;
+  if (n_jobs < 128) return false;
+  const int most = n_jobs < 136 ? 5 : n_jobs < 172 ? 11 : n_jobs < 216 ? 10 : n_jobs <= 544 ? 16 : n_jobs < 608 ? 6 : 8;
+  return n_slices <= most || n_slices == 16 || (n_slices == 8 && n_jobs >= 136);
+}
+
 }  // namespace
 
 int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
@@ -1496,16 +1516,8 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
   for (int s = 0; s < P.n_window; ++s) at |= reinterpret_cast<uintptr_t>(P.layer[s].q) | reinterpret_cast<uintptr_t>(P.layer[s].k);
   const bool pipe_fits = n_jobs > 0 && row_tiles == 4 && P.force_window == 0 && P.n_slices <= kPipeMaxSlices &&
                          P.n_slices <= pipe_wg && at % 16 == 0;
-  // Of those, the window kernels are the faster ones once the chip is full and either
-  //   - rows are padded (fewer than 128, or a window that is no multiple of 32): the pipelined
-  //     kernel then masks every tile (30 layers at L = 4096, two query heads per KV head: 163 us
-  //     a call against 114; 32 jobs of 1024 keys: 30 against 37, so from 128 jobs or 1024 items), or
-  //   - a job has few slices: its two-level exchange is then a large share of an item (30 layers at
-  //     L = 1024: 72 us against 53, batch 8: 373 against 309; at 16 slices 94 against 75, but at 12
-  //     slices and 1920 jobs 389 against 403, and 32 slices are even or better in the pipeline).
   const bool padded = P.group * ntg < 4 || P.window != 32 * ntg;
-  const bool window_wins = padded ? n_jobs >= 128 || (int64_t)n_jobs * P.n_slices >= 1024
-                                  : n_jobs >= 128 && P.n_slices <= (n_jobs < 1024 ? 16 : 8);
+  const bool window_wins = window_faster(n_jobs, P.n_slices, padded, pipe_wg);
   const bool pipe = pipe_fits && !window_wins;
   const dim3 prep_grid(n_jobs * kPrepParts), prep_block(kPrepThreads);
   if (pipe) {
