@@ -240,7 +240,11 @@ int rkv_prefill_workspace_size(const rkv_plan* plan, const rkv_shape* shape, siz
  * 88 natural-log units above that reference overflows that path.  A SNAPKV / H2O job where
  * this happens is rescored exactly on the device before selection (RKV_STATUS_REPAIRED; outputs
  * valid); an H2O_FULL layer reports RKV_STATUS_INVALID.  TOVA is exact by construction (per-head
- * running maxima).  The status word (rkv_prefill_check) must be clean of RKV_STATUS_TIMEOUT and
+ * running maxima).  Sums are 32-bit in a fixed order, so a call repeated on the same inputs gives the
+ * same bits; which kernel scores a job depends on the whole call (jobs, prompt length, alignment), so
+ * the same sequence in a call of other layers or sequences may differ in the last bits of its scores,
+ * and in the order of positions whose scores differ by no more than that.
+ * The status word (rkv_prefill_check) must be clean of RKV_STATUS_TIMEOUT and
  * RKV_STATUS_INVALID for the outputs to be valid; the call itself cannot report them, since
  * it returns before the kernels run.
  * ws: caller-owned device workspace of at least rkv_prefill_workspace_size bytes, 256-byte
@@ -288,6 +292,8 @@ int rkv_prefill_check(const void* ws, size_t ws_bytes, int32_t* status_out);
  *   read nor written (state->acc[l] may be NULL for such a layer).
  * STREAMING: the slot with the smallest position >= n_sink is replaced by the new token.
  * FULL: the layer is skipped.
+ * Sums are 32-bit in a fixed order that depends on the whole step (the number of its workgroups and its
+ * largest capacity choose their threads), so a sequence's acc may differ in the last bits in another batch.
  * Errors: as rkv_prefill_evict; RKV_ERR_SHAPE if position < C.  Every layer is validated
  * before the first launch: a failed call enqueues nothing. */
 int rkv_decode_step(const rkv_plan* plan, const rkv_shape* shape, const rkv_decode_state* state,
@@ -319,10 +325,9 @@ int rkv_decode_init_from_prefill(const rkv_plan* plan, const rkv_shape* shape, c
  *   (n_q = L profiles every query); k[l]: bf16 [B, Hkv, L, d].  Device pointers, host arrays.
  * rows_out: device fp32 [n_layers, B, Hq, n_q], every profiled row's entropy;
  * h_out: device fp32 [n_layers]; status: device uint32, cleared by the call's first launch and
- *   then OR-ed into: bit 0 (1) when some row is not finite (h_out is then invalid), bit 2 (4)
- *   when a block of rows overflowed the fast path's per-row reference (a logit more than ~88
- *   natural-log units above the larger of the row's logits with its own key and with key 0)
- *   and was recomputed exactly (results valid).
+ *   then OR-ed into: bit 0 (1) when some row is not finite (h_out is then invalid), for instance
+ *   because it overflowed the per-row reference (a logit more than ~88 natural-log units above
+ *   the larger of the row's logits with its own key and with key 0).
  * ws: caller-owned device workspace of at least rkv_entropy_workspace_size bytes (8-byte
  *   aligned; per-block partial sums).  Enqueued on `stream`; no allocation.
  * Errors: RKV_ERR_INVALID_ARG (null pointers, n_layers < 1, n_q outside [1, L]), RKV_ERR_SHAPE,
@@ -336,7 +341,9 @@ int rkv_entropy_profile(const rkv_shape* shape, int32_t n_layers, int32_t n_q, c
 /* Implementation calls (measurement, no paper passage): kernel timing for benchmarks and tests.
  * rkv_profile_enable(stage) makes every following
  * launch of that stage record a pair of HIP events around it on the caller's stream
- * (stage: 0 counter reset, 1 scoring, 2 selection, 3 gather, 4 decode; -1 disables).
+ * (stage: 0 what precedes scoring (the pipelined kernel's preparation, or the status reset of a call
+ * without window-scored layers; the window kernels have none), 1 scoring, 2 selection, 3 gather, 4 decode;
+ * -1 disables).
  * Up to 4096 launches are kept.  rkv_profile_read synchronises on the recorded events,
  * returns the number of launches and their summed duration in milliseconds, and clears
  * the record.  Host-side state shared by all threads. */

@@ -114,9 +114,8 @@ int score_class(const rkv_layer& ly, const Layout& lo) {
   return 0;
 }
 
-// Test hook: RKV_FORCE_WINDOW=1 selects the window scoring kernels (normally used for prompts of
-// more than 64 slices and for eight row tiles) on layouts the pipelined kernel would take, so
-// that they can be checked on short prompts too.
+// Test hook: RKV_FORCE_WINDOW=1 selects the window scoring kernels for calls that the pipelined kernel would
+// take too (launch_prefill has the rule), so that every layout can be checked through them.
 int force_window() {
   const char* e = std::getenv("RKV_FORCE_WINDOW");
   return e && std::atoi(e) > 0 ? 1 : 0;

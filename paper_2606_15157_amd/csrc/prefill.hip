@@ -12,8 +12,8 @@
 //     once, publishes per-row sums against a fixed per-row reference logit, and turns its
 //     exponentials into probabilities once the job's sums are in (two levels: per slice group,
 //     then per job; the kernel's own comment below has the schedule);
-//   window kernels (window.hip; the other calls, and those where they are faster: launch_prefill has
-//     the rule): row sums, then column sums, each streaming K once;
+//   window kernels (window.hip; the other calls, and those where they are faster:
+//     window_faster has the rule): row sums, then column sums, each streaming K once;
 //   select kernels (one workgroup per job): repair the pooled score next to slice borders (or
 //     rescore a job flagged for a reference overflow exactly), find the k-th largest score with
 //     at most three radix-histogram passes and write the retained positions in ascending order;

@@ -162,7 +162,7 @@ struct EntropyLaunch {
   float* rows;        // [n_layers, B, Hq, n_q] row entropies (nats)
   float* h;           // [n_layers] mean row entropy
   double* partial;    // [n_layers, B * Hkv * ceil(n_q / 32)] per-workgroup sums of row entropies
-  uint32_t* status;   // bit 0: some row entropy is not finite; bit 2: a block was recomputed exactly
+  uint32_t* status;   // bit 0: some row entropy is not finite
   int32_t first_group;  // 1 in the call's first launch: it clears the status word
 };
 

@@ -1,6 +1,7 @@
-// Window scoring for prompts outside the pipelined kernel's range (more than 64 slices of 128
-// keys per job, or eight row tiles: G * ceil(w / 32) > 4) on gfx950.  Per (sequence, layer, KV
-// head) job the scores are those of the pipelined kernel (Section 2.1's SnapKV and H2O rules):
+// Window scoring on gfx950 where the pipelined kernel does not apply (more than 64 slices of 128 keys per
+// job, eight row tiles: G * ceil(w / 32) > 4, inputs that are not 16-byte aligned) or is the slower one (many
+// jobs of padded rows or of few slices; window_faster has the rule).  Per (sequence, layer, KV head)
+// job the scores are those of the pipelined kernel (Section 2.1's SnapKV and H2O rules):
 //   A[g][j] = sum_i softmax_j(Q[g,i] . K[j] / sqrt(d)), S = mean_g maxpool(A[g]) or mean_g A[g],
 // computed in two passes over the keys instead of one pass with a cross-workgroup exchange.
 //
@@ -30,9 +31,10 @@
 //
 // Bound: issue of the exponentials and MFMAs (per 64 logits 16 cycles of multiply-add, exponential
 // and addition, beside 16 of the matrix pipe, half of which hold back the VALU too), at the clock the
-// power limit leaves (1.65 GHz).  At 960 jobs of 256 rows and 32768 keys the rows pass takes 1.93 ms
-// (2.38 with 16x16x32 MFMA and 32 rows per wave, 1.09 PFLOP/s now) and the columns pass 2.39 ms
-// (3.04).  Four row tiles are bound by the second reading of the keys: 128 jobs of 20011 keys, 656 MB
+// power limit leaves (1.6 GHz).  With eight row tiles the rows pass has the VALU busy 0.84 and the matrix pipe 0.74
+// of the time, the columns pass 0.62 and 0.49, its waves waiting (barriers, stores) for 0.29.  At 960 jobs of
+// 256 rows and 32768 keys the rows pass takes 1.93 ms (2.38 with 16x16x32 MFMA and 32 rows per wave, 1.09
+// PFLOP/s now) and the columns pass 2.39 ms (3.04).  Four row tiles are bound by the second reading of the keys: 128 jobs of 20011 keys, 656 MB
 // a pass, 140 and 128 us (150 and 216).
 #include <hip/hip_runtime.h>
 

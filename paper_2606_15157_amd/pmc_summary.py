@@ -7,8 +7,10 @@
     python -m paper_2606_15157_amd.pmc_summary <dir_fetch> <dir_write> <out.json> <out.md>
 
     python -m paper_2606_15157_amd.pmc_summary --sq <out.md> <dir> [<dir> ...]
+    python -m paper_2606_15157_amd.pmc_summary --kernels <out.md> "<title>" "<command>" <name>,<name>.. <dir> [<dir> ...]
 
-The second form tabulates SQ counters of the scoring kernel from one or more rocprofv3 --pmc
+The third form tabulates SQ counters of several kernels (the median over each one's dispatches) side by side,
+with the clock that GRBM_GUI_ACTIVE and the dispatches' timestamps give.  The second form tabulates SQ counters of the scoring kernel from one or more rocprofv3 --pmc
 runs (median over the kernel's dispatches in each run): shares of SQ_WAVE_CYCLES and instruction
 counts per wave and per pipeline iteration.
 
@@ -149,8 +151,47 @@ def sq_main(out_md, dirs, iterations=64):
     print(open(out_md).read())
 
 
+def kernels_main(out_md, title, command, names, dirs):
+    """One column per kernel of `names` (parts of kernel names): SQ counters as shares of the wave cycles, instructions a wave, clock."""
+    vals = {n: {} for n in names}
+    sets = []
+    for d in dirs:
+        path = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
+        rows = list(csv.DictReader(open(path[0])))
+        sets.append(sorted({r["Counter_Name"] for r in rows}))
+        for c in sets[-1]:
+            per = per_dispatch(d, c)
+            for n in names:
+                vals[n][c] = statistics.median(pick(per, n)[1])
+        for n in names:   # busy cycles, summed over the eight XCDs, over the time of dispatches long enough for the ratio
+            ghz = [float(r["Counter_Value"]) / 8 / (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) for r in rows
+                   if n in r["Kernel_Name"] and r["Counter_Name"] == "GRBM_GUI_ACTIVE"
+                   and int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) > 500000]
+            if ghz:
+                vals[n]["clock"] = statistics.median(ghz)
+    with open(out_md, "w") as f:
+        f.write(f"# {title}\n\nCommands (one run per counter set; median over the dispatches of each run):\n\n")
+        for cs in sets:
+            f.write(f"    rocprofv3 --pmc {' '.join(cs)} --output-format csv -d <dir> -o run -- {command}\n")
+        f.write("\nSQ_WAVE_CYCLES and the SQ_WAIT / SQ_ACTIVE counters count quads of clocks, SQ_VALU_MFMA_BUSY_CYCLES clocks: "
+                "the matrix pipe's share below is half of their ratio (two waves a SIMD).\n")
+        short = [n.replace("rkv::(anonymous namespace)::", "") for n in names]
+        f.write("\n| | " + " | ".join(f"`{n}`" for n in short) + " |\n|---|" + "---|" * len(names) + "\n")
+        f.write("| matrix pipe busy | " + " | ".join(f"{vals[n]['SQ_VALU_MFMA_BUSY_CYCLES'] / 2 / vals[n]['SQ_WAVE_CYCLES']:.2f}" for n in names) + " |\n")
+        for c in SQ_SHARES[1:]:
+            if c != "SQ_VALU_MFMA_BUSY_CYCLES" and all(c in vals[n] for n in names):
+                f.write(f"| {c} / SQ_WAVE_CYCLES | " + " | ".join(f"{vals[n][c] / vals[n]['SQ_WAVE_CYCLES']:.3f}" for n in names) + " |\n")
+        for c in SQ_COUNTS:
+            if all(c in vals[n] for n in names):
+                f.write(f"| {c} a wave | " + " | ".join(f"{vals[n][c] / vals[n]['SQ_WAVES']:.0f}" for n in names) + " |\n")
+        f.write("| clock (GHz) of dispatches over 0.5 ms | " + " | ".join(f"{vals[n]['clock']:.2f}" if "clock" in vals[n] else "" for n in names) + " |\n")
+    print(open(out_md).read())
+
+
 if __name__ == "__main__":
     if len(sys.argv) > 1 and sys.argv[1] == "--sq":
         sq_main(sys.argv[2], sys.argv[3:])
+    elif len(sys.argv) > 1 and sys.argv[1] == "--kernels":
+        kernels_main(sys.argv[2], sys.argv[3], sys.argv[4], sys.argv[5].split(","), sys.argv[6:])
     else:
         main(sys.argv)
