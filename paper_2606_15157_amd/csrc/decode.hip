@@ -324,12 +324,15 @@ int launch_decode_group(const DecodeLaunch& D, int max_capacity, hipStream_t st)
   const size_t lds = sizeof(float) * (size_t)(G + 1) * (max_capacity + 1);
   // Twice the waves a workgroup, so twice the key rows in flight, where the workgroups leave a CU few of them:
   // one workgroup per CU (256 of 512 entries: 16.0 -> 13.4 us, of 2048: 44 -> 31; below 128 entries a second
-  // block of rows is empty: 64: 7.1 -> 8.0), or at most five by their LDS with more of them waiting (4096 of
-  // 2048 entries: 383 -> 362, eight heads a group 729 -> 571).  Otherwise the smaller ones end more evenly (512
-  // of 512 entries: 19.7 against 20.8; 16384 of 1024: 716 against 726).  Four times the waves measured
-  // slower everywhere (256 of 512: 16.1, 16384 of 1024: 1233).
+  // block of rows is empty: 64: 7.1 -> 8.0), or few by their LDS with more of them waiting.  With eight heads a group that
+  // is three (2048 workgroups of 1500 entries: 274 -> 216 us, of 2048 376 -> 294): the registers leave 20 waves a
+  // CU, so four of 512 threads do not fit where four of 256 do (of 1000 entries 141 -> 152, 6144 of them 384 ->
+  // 434).  With fewer heads it is four (2048 of 4000 entries at four heads 430 -> 379, of 2048 203 -> 197, of 3000 at
+  // two 281 -> 278; five: 1500 at four 143.7 -> 143.9, 4000 at one 351 -> 359).  Otherwise the smaller ones end more
+  // evenly (512 of 512 entries: 19.7 against 20.8; 16384 of 1024: 716 against 726).  Four times the waves
+  // measured slower everywhere (256 of 512: 16.1, 16384 of 1024: 1233).
   const size_t by_lds = 160 * 1024 / lds;
-  const bool wide = grid <= 256 ? max_capacity >= 128 : by_lds <= 5 && grid > 256 * by_lds;
+  const bool wide = grid <= 256 ? max_capacity >= 128 : by_lds <= (G == 8 ? 3 : 4) && grid > 256 * by_lds;
   return wide ? launch_decode_kernel<G, 512>(D, grid, lds, st) : launch_decode_kernel<G, 256>(D, grid, lds, st);
 }
 

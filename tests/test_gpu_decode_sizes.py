@@ -12,8 +12,9 @@ SHAPES = [
     (1, 4, 1, 2), (1, 8, 2, 63), (1, 8, 2, 127), (1, 8, 2, 128), (1, 8, 1, 129), (2, 2, 2, 255), (1, 4, 2, 513),
     (1, 8, 2, 1023), (1, 8, 2, 1024), (1, 16, 2, 1025), (1, 8, 2, 2049),
     (65, 8, 2, 129), (65, 8, 2, 1025),        # more than 256 workgroups: 256 threads
-    # eight heads a group: four workgroups a CU by LDS and 800 of them, 256 threads; 1200, 512; two and 520, 512; nine, 256
-    (200, 16, 2, 1100), (300, 16, 2, 1100), (130, 16, 2, 2049), (200, 16, 2, 500),
+    # eight heads a group: four workgroups a CU by LDS, 256 threads; three and 1200, 512; two and 520, 512; nine, 256
+    (200, 16, 2, 1100), (300, 16, 2, 1400), (130, 16, 2, 2049), (200, 16, 2, 500),
+    (260, 8, 2, 1800), (200, 8, 2, 1800),     # four heads: four and 1040, 512 threads; 800, 256
 ]
 
 
@@ -21,14 +22,14 @@ def threads(B, hq, hkv, C):
     """(threads, workgroups a CU by LDS, whether there are more than 256 workgroups) of the two-layer step below:
     the rule of the launch, kept alike with csrc/decode.hip."""
     grid, by_lds = 2 * B * hkv, 160 * 1024 // (4 * (hq // hkv + 1) * (C + 1))
-    wide = C >= 128 if grid <= 256 else by_lds <= 5 and grid > 256 * by_lds
+    wide = C >= 128 if grid <= 256 else by_lds <= (3 if hq // hkv == 8 else 4) and grid > 256 * by_lds
     return 512 if wide else 256, min(by_lds, 6), grid > 256
 
 
 def test_shapes_take_every_branch():
     got = {threads(*s) for s in SHAPES}
     assert {(t, many) for t, _, many in got} == {(256, False), (512, False), (256, True), (512, True)}
-    assert {(512, 2, True), (512, 4, True), (256, 4, True), (256, 6, True)} <= got
+    assert {(512, 2, True), (512, 3, True), (512, 4, True), (256, 4, True), (256, 6, True)} <= got
 
 
 @pytest.mark.parametrize("B,hq,hkv,C", SHAPES, ids=[f"b{s[0]}_{s[1]}x{s[2]}_c{s[3]}" for s in SHAPES])
