@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, 2) void fullspan_rows_kernel(const PrefillLaun
 }
 
 // KG waves share the query rows of a key group of 64: one takes every row (256 keys a workgroup), two a subtile
-// of each tile, four a subtile of every other tile.
+// of each tile, four a subtile of each pair of tiles.
 template <int G, int KG>
 __global__ __launch_bounds__(256, 2) void fullspan_cols_kernel(const PrefillLaunch P) {
   constexpr int RG = 4 / KG, kKeys = 64 * RG, kDma = kTileDma + 1;
@@ -117,25 +117,35 @@ __global__ __launch_bounds__(256, 2) void fullspan_cols_kernel(const PrefillLaun
     }
   };
   const uint32_t lds0 = lds_addr(&sQ[0][0]), lam0 = lds_addr(&sLam[0][wv][0]);
-  stream_tiles<kDma>(n, [&](int t, int buf) __attribute__((always_inline)) {
+  auto issue = [&](int t, int buf) __attribute__((always_inline)) {
     const int g = t % G, t0 = (p_last - t / G) * kTile;
     issue_tile(qbase + (size_t)g * L * kHeadDim, t0, L, lds0 + buf * (kTileHalfs * 2), wv);
     dma4(lamj + (size_t)g * L + min(t0 + lane, L - 1), lam0 + buf * (4 * kTile * 4));
-  }, [&](auto buf, int t) __attribute__((always_inline)) {
-    constexpr int b = decltype(buf)::value;
-    if (t >= nw) return;   // before the wave's keys, not yet before the workgroup's
-    const int t0 = (p_last - t / G) * kTile;
-    const float* lam = &sLam[b][wv][0];
-    if constexpr (KG == 1) {
-      step(sQ[b], lam, 0, t0, accA, nA, accB, nB);
-      step(sQ[b], lam, 1, t0 + 32, accB, nB, accA, nA);
-    } else {
-      const int sub = kg & 1;
-      if (KG == 4 && (kg >> 1) != (b & 1)) return;
-      if constexpr ((KG == 2 ? b : b >> 1) % 2 == 0) step(sQ[b], lam, sub, t0 + 32 * sub, accA, nA, accB, nB);
-      else step(sQ[b], lam, sub, t0 + 32 * sub, accB, nB, accA, nA);
-    }
-  });
+  };
+  if constexpr (KG == 4) {
+    stream_pairs<kDma>(n, issue, [&](auto at, int p) __attribute__((always_inline)) {
+      const int sub = kg & 1, t = 2 * p + (kg >> 1), buf = 2 * decltype(at)::value + (kg >> 1);
+      if (t >= nw) return;   // before the wave's keys, or a last tile without a partner
+      const int t0 = (p_last - t / G) * kTile + 32 * sub;
+      if constexpr (decltype(at)::value == 0) step(sQ[buf], &sLam[buf][wv][0], sub, t0, accA, nA, accB, nB);
+      else step(sQ[buf], &sLam[buf][wv][0], sub, t0, accB, nB, accA, nA);
+    });
+  } else {
+    stream_tiles<kDma>(n, issue, [&](auto buf, int t) __attribute__((always_inline)) {
+      constexpr int b = decltype(buf)::value;
+      if (t >= nw) return;   // before the wave's keys, not yet before the workgroup's
+      const int t0 = (p_last - t / G) * kTile, sub = kg;
+      const float* lam = &sLam[b][wv][0];
+      if constexpr (KG == 1) {
+        step(sQ[b], lam, 0, t0, accA, nA, accB, nB);
+        step(sQ[b], lam, 1, t0 + 32, accB, nB, accA, nA);
+      } else if constexpr (b % 2 == 0) {
+        step(sQ[b], lam, sub, t0 + 32 * sub, accA, nA, accB, nB);
+      } else {
+        step(sQ[b], lam, sub, t0 + 32 * sub, accB, nB, accA, nA);
+      }
+    });
+  }
   const int subtiles = KG == 4 ? (nw + 1 - (kg >> 1)) >> 1 : nw;   // this wave's, where it takes one of a tile
   if (KG == 1 || (subtiles & 1) == 0) {
 #pragma unroll
@@ -184,12 +194,14 @@ int launch_group(const PrefillLaunch& P, int n_full, hipStream_t st) {
   }
   if (!small) launch_rows<8, G>(P, n_full, st);
   // Key groups: every query tile a workgroup brings in serves 256, 128 or 64 keys, so as many as leave enough
-  // workgroups for an even end (1024 of 256 keys: 2045 us a call against 2160 with twice as many of 128;
-  // 512: 1130 against 1005; 320: 195 against 155), and 64 where the chip would be nearly empty (64: 140 us
-  // with 128 keys, 136 with 64).
+  // workgroups for an even end.  In blocks of 256 keys: 1024 of them 2045 us a call against 2160 with 128 keys,
+  // 576 310 against 310 at L = 1500, 512 1130 against 1005.  64 keys, four waves on a pair of tiles, have the
+  // shortest chain of tiles (one job of 840 keys at four heads 54 us against 82 with 128 keys); they are the faster ones up
+  // to 128 such blocks at one head a group (192: 52 against 51 us; 288: 78, 72), 256 at two (75, 78; 384: 135, 132) and
+  // about 320 from four on (288: 171, 181; 384: 136, 142 at L = 840 and 214, 211 at L = 1500).
   auto blocks = [&](int keys) { return (unsigned)(n_full * ((L + keys - 1) / keys)); };
   if (blocks(256) >= 768) fullspan_cols_kernel<G, 1><<<blocks(256), 256, 0, st>>>(P);
-  else if (blocks(256) > 64) fullspan_cols_kernel<G, 2><<<blocks(128), 256, 0, st>>>(P);
+  else if (blocks(256) > (G == 1 ? 128 : G == 2 ? 256 : 320)) fullspan_cols_kernel<G, 2><<<blocks(128), 256, 0, st>>>(P);
   else fullspan_cols_kernel<G, 4><<<blocks(64), 256, 0, st>>>(P);
   return (int)hipGetLastError();
 }

@@ -111,6 +111,31 @@ __device__ __forceinline__ void stream_tiles(int n, Issue&& issue, Body&& body) 
   }
 }
 
+// The same with the tiles two at a time, 2 p and 2 p + 1 in buffers 2 (p % 2) and 2 (p % 2) + 1, and
+// `body(p % 2, p)`: one barrier for both, so that waves which take a tile of the pair each work side by side.
+// A last tile without a partner is requested twice.
+template <int kDma, typename Issue, typename Body>
+__device__ __forceinline__ void stream_pairs(int n, Issue&& issue, Body&& body) {
+  const int np = (n + 1) / 2;
+  auto request = [&](int p, int at) __attribute__((always_inline)) {
+    issue(2 * p, 2 * at);
+    issue(min(2 * p + 1, n - 1), 2 * at + 1);
+  };
+  request(0, 0);
+  auto one = [&](auto at, int p) __attribute__((always_inline)) {
+    constexpr int b = decltype(at)::value;
+    wait_tile<kDma>(0);
+    tile_barrier();
+    if (p + 1 < np) request(p + 1, 1 - b);   // every wave is past pair p - 1
+    body(at, p);
+  };
+#pragma unroll 1
+  for (int p = 0; p < np; p += 2) {
+    one(std::integral_constant<int, 0>{}, p);
+    if (p + 1 < np) one(std::integral_constant<int, 1>{}, p + 1);
+  }
+}
+
 // Byte offset inside a tile of this lane's fragment of k-step st (rows sub * 32 + lane % 32, 16-byte
 // chunk 2 st + lane / 32): tile_lane() ^ (32 st), plus 8192 sub.
 __device__ __forceinline__ uint32_t tile_lane() {

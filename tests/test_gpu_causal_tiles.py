@@ -52,8 +52,12 @@ FULL = [
     # L, B, Hq, Hkv
     (1, 1, 4, 1), (31, 1, 4, 1), (64, 1, 2, 2), (65, 2, 4, 2), (127, 1, 8, 1), (193, 1, 8, 2), (256, 1, 16, 2),
     (257, 1, 1, 1), (321, 2, 2, 1), (640, 1, 8, 2),
-    (129, 8, 32, 8),                        # 64 blocks of 256 keys: four key groups
-    (129, 9, 32, 8), (300, 5, 32, 16), (200, 20, 32, 4),      # 72, 160 and 80: two
+    (129, 8, 32, 8), (129, 9, 32, 8), (300, 5, 32, 16), (200, 20, 32, 4),   # 64 to 160 blocks of 256 keys: four key groups
+    (150, 160, 16, 8), (150, 35, 64, 8),    # 1280 and 280: one and four
+    (300, 8, 8, 8), (300, 9, 8, 8),         # one head a group, 128 and 144: four and two
+    (300, 16, 16, 8), (300, 17, 16, 8),     # two heads, 256 and 272: four and two
+    (300, 20, 32, 8), (300, 21, 32, 8),     # four heads, 320 and 336: four and two
+    (300, 41, 32, 4),                       # eight heads, 328: two
     (259, 48, 8, 8), (300, 64, 16, 8),      # 768 and 1024: one; four and eight row tiles
     (259, 48, 32, 8), (259, 96, 32, 4),     # 768: one, four and eight heads per group
     (700, 125, 12, 3),                      # 4125 blocks of query rows: job by job, 375 jobs in rounds of eight
@@ -100,6 +104,8 @@ def test_unaligned_inputs():
     q, k = gen(45, 1, 8, L, 128), gen(46, 1, 2, L, 128)
     a, b = rkv.entropy_profile([q], [k]), rkv.entropy_profile([shifted(q)], [shifted(k)])
     assert torch.equal(a["rows"], b["rows"]) and torch.equal(a["h"], b["h"])
+    assert torch.equal(full_span(q, k)[0], full_span(shifted(q), shifted(k))[0])
+    q = gen(45, 1, 2, L, 128)   # one head a group: an odd number of query tiles for every second key block
     assert torch.equal(full_span(q, k)[0], full_span(shifted(q), shifted(k))[0])
 
 
