@@ -331,9 +331,6 @@ __global__ __launch_bounds__(kPipeThreads, 1) void score_pipe_kernel(const Prefi
   const float sl2 = P.scale_log2;
   const float inv_g = 1.f / (float)G;
   uint32_t* status = P.counters;
-  // Only short runs have padded rows (window_faster).  The long-run form keeps their code
-  // all the same: without it its registers are dealt differently and the 32-layer route at 8K takes 207.0 us
-  // against 206.0, at batch 8 1458 against 1444.
   const bool padded_rows = (G * NTH < 4) || (w != NTH * 32);
 
   const int64_t first = blockIdx.x;
@@ -1478,24 +1475,58 @@ void launch_staged(int stage, void (*kernel)(KArgs...), dim3 grid, dim3 block, s
     hipLaunchKernelGGL(kernel, grid, block, shmem, st, args...);
 }
 
-// Whether the window kernels are the faster ones for a call that the pipelined kernel could take.  Times are of
-// a call, pipelined / window, on 256 workgroups.
-//   Padded rows (fewer than 128, or a window that is no multiple of 32): the pipelined kernel masks every tile.
-//   With 128 jobs 1.01 to 1.5 of the window kernels' time whatever the length, and with fewer from its long-run
-//   form on: 16 jobs of 64 slices (its last short run) 43 us / 47, 32 of 32 44 / 44, 24 of 48 50 / 46, 80 of
-//   13 1.04, 32 of 64 63 / 53.
-//   Otherwise: its two-level exchange is a large share of an item where a job has few slices, and every pass
-//   over the workgroups ends with a whole job where their count is a multiple of the slices: the same ones then
-//   always take a group's sums (240 jobs of 7, 8, 9 slices: 1.18, 1.29, 1.06; 16 slices 1.03 to 1.19 from 128
-//   jobs on, 17 slices 0.84 to 1.01).  The window kernels have 512 workgroups resident and fill them evenly up to as
-//   many jobs.  The most slices at which they are not the slower ones, and the ratio there and one further:
-//   128 jobs 5 (1.04, 0.94), 152 11 (1.02, 0.98), 192 10 (1.02, 0.97), 240 to 512 16 (1.18, 0.94), 576 6 (1.02,
-//   0.91) and 8 (1.12), 640 to 1536 8 (1.15, 0.94).
-bool window_faster(int n_jobs, int n_slices, bool padded, int pipe_wg) {
-  if (padded) return n_jobs >= 128 || (int64_t)n_jobs * n_slices > (int64_t)kPipeShortItems * pipe_wg;
-  if (n_jobs < 128) return false;
-  const int most = n_jobs < 136 ? 5 : n_jobs < 172 ? 11 : n_jobs < 216 ? 10 : n_jobs <= 544 ? 16 : n_jobs < 608 ? 6 : 8;
-  return n_slices <= most || n_slices == 16 || (n_slices == 8 && n_jobs >= 136);
+// Whether the window kernels are the faster ones for a call that the pipelined kernel could take.  Measured: both
+// on 256 workgroups at 47 job counts of 128 to 1536 and 2 to 24 slices (to 64 with padded rows), every layer
+// H2O, every layer SnapKV and half of each, with the keys out of the last-level cache and partly in it; ratios below are
+// pipelined / window time of the whole call, keys out of the cache.
+//   The window kernels give each job a workgroup (few jobs: several), at most 512 resident, so their time steps up where
+//   a wave of 256 jobs has just been passed and falls per job until the next: 10 slices 256 jobs 1.15, 264
+//   0.87, 384 0.98, 512 1.05, 520 0.83, 768 0.99.  So the lines lie by the place of the job count between multiples of 256.
+//   Whole tiles: the pipelined kernel's two-level exchange is a large share of an item where a job has few
+//   slices, and every pass over the workgroups ends with a whole job where their count is a multiple of the
+//   slices: the same ones then always take a group's sums (8 slices 1.10 to 1.36 and 16 slices 0.97 to 1.22
+//   outside the first jobs of a wave).  Ratio at the last slice count taken and one further: 128 jobs 5 (1.00,
+//   0.92), 160 11 (1.04, 0.99), 192 10 (1.03, 0.95), 208 13 (1.01, 0.99), 224 16 (1.22, 0.97), 256 16 (1.15, 0.93), 288 6 (1.02, 0.97), 352
+//   8 (1.19, 0.94), 384 10 (0.98, 0.93), 416 11 (1.03, 0.98), 448 13 (0.99, 0.95), 512 16 (1.18, 0.98), 520 5 (1.00,
+//   0.93), 576 6 (1.04, 0.94), 640 to 1536 8 (1.10 to 1.25, 0.92 to 1.03), 768 and
+//   1024 10 (0.99 and 1.00, 0.93 and 1.00).
+//   Rows that do not fill their tiles: the pipelined kernel masks every tile.  Fewer than 128 jobs: window from the
+//   pipelined kernel's long-run form on (32 jobs of 34 slices 1.01, 104 of 11 1.03), not yet 80 of 14 (0.93) and
+//   96 of 11 (1.00).  From 128 on with four tiles in use 0.96 to 1.5, but for 520 jobs of 28 slices (0.92).
+//   With empty tiles too, whose exponentials the window kernels take as well, it is the same where every layer
+//   pools, and with some of them they lose where a wave has just been passed: 264 jobs 17 slices 1.01, 20 0.95; 520
+//   14 0.98, 20 0.92; elsewhere 0.94 to 1.4.  Without SnapKV layers: 176 jobs 28 slices 1.00, 52 0.94; 264 17
+//   1.04, 20 0.94; 352 24 0.98, 46 0.92; 416 34 1.01, 52 0.98; 520 11 1.00, 17 0.96; 544 14 1.02, 20 0.96; 576 17 1.01, 20
+//   0.95; 832 17 1.01, 28 0.96; 960 24 1.06, 46 0.97.
+//   Over 3300 calls of ordinary shapes none takes more than 4 % longer than with the pipelined kernel for all that fit it.
+// n_snap: how many of the n_layers layers pool.
+bool window_faster(int n_jobs, int n_slices, bool padded, bool empty_tiles, int n_snap, int n_layers, int pipe_wg) {
+  const int at = (n_jobs - 1) % 256;   // place in the wave of 256 jobs
+  if (!padded) {
+    if (n_jobs < 128) return false;
+    int most;
+    if (n_jobs <= 256) most = n_jobs < 136 ? 5 : n_jobs < 152 ? 6 : n_jobs < 176 ? 11 : n_jobs < 200 ? 10 : n_jobs < 224 ? 13 : 16;
+    else if (n_jobs <= 512) most = at < 79 ? 6 : at < 127 ? 8 : at < 159 ? 10 : at < 191 ? 11 : at < 223 ? 13 : 16;
+    else most = n_jobs < 560 ? 5 : n_jobs < 640 ? 6 : at >= 207 ? 10 : 8;
+    return n_slices <= most || (n_slices == 8 && n_jobs >= 136 && at >= 47) || (n_slices == 16 && at >= 31) ||
+           (n_jobs >= 136 && n_jobs < 152 && n_slices >= (n_jobs < 144 ? 10 : 8) && n_slices <= 11);
+  }
+  if (n_jobs < 128)
+    return (int64_t)n_jobs * n_slices > (int64_t)kPipeShortItems * pipe_wg && n_slices > (n_jobs < 96 ? 16 : n_jobs < 104 ? 11 : 9);
+  int most = kPipeMaxSlices;
+  if (!empty_tiles || n_snap == n_layers) {
+    if (n_jobs > 512 && n_jobs < 544) most = 17;
+  } else if (n_snap > 0) {
+    if (n_jobs > 256 && n_jobs < 273) most = 17;
+    else if (n_jobs > 512 && n_jobs < 560) most = 14;
+  } else if (n_jobs <= 256) {
+    if (n_jobs >= 168 && n_jobs < 184) most = 28;
+  } else if (n_jobs <= 512) {
+    if (at < 191) most = at < 48 ? 17 : at < 80 ? 40 : at < 112 ? 24 : 34;
+  } else {
+    most = n_jobs < 544 ? 11 : n_jobs < 576 ? 14 : n_jobs < 640 || at < 96 ? 17 : 24;
+  }
+  return n_slices <= most;
 }
 
 }  // namespace
@@ -1516,8 +1547,10 @@ int launch_prefill(const PrefillLaunch& P, int row_tiles, void* stream) {
   for (int s = 0; s < P.n_window; ++s) at |= reinterpret_cast<uintptr_t>(P.layer[s].q) | reinterpret_cast<uintptr_t>(P.layer[s].k);
   const bool pipe_fits = n_jobs > 0 && row_tiles == 4 && P.force_window == 0 && P.n_slices <= kPipeMaxSlices &&
                          P.n_slices <= pipe_wg && at % 16 == 0;
-  const bool padded = P.group * ntg < 4 || P.window != 32 * ntg;
-  const bool window_wins = window_faster(n_jobs, P.n_slices, padded, pipe_wg);
+  const bool empty_tiles = P.group * ntg < 4, padded = empty_tiles || P.window != 32 * ntg;
+  int n_snap = 0;
+  for (int s = 0; s < P.n_window; ++s) n_snap += P.layer[s].rule == RKV_SNAPKV;
+  const bool window_wins = window_faster(n_jobs, P.n_slices, padded, empty_tiles, n_snap, P.n_window, pipe_wg);
   const bool pipe = pipe_fits && !window_wins;
   const dim3 prep_grid(n_jobs * kPrepParts), prep_block(kPrepThreads);
   if (pipe) {

@@ -40,10 +40,27 @@ def test_window_tile_edges(L, w, hq, hkv, pool, monkeypatch):
                          ids=["few_slices", "nine_slices", "padded_window", "padded_heads"])
 def test_many_jobs_take_the_window_kernels(L, w, hq, hkv):
     """128 jobs, from which the window kernels take padded layouts and unpadded ones of up to five slices, or 160
-    of up to eleven."""
+    of up to eleven (few_slices, nine_slices)."""
     n = 20 if L == 1100 else 16
     layers = [[gen(32, 0, l, L, w=w, Hq=hq, Hkv=hkv)] for l in range(n)]
     run_case([OP.SNAPKV, OP.H2O] * (n // 2), [60] * n, layers, window=w, label=f"many_L{L}_w{w}")
+
+
+@pytest.mark.parametrize("L,w,hq,rules", [(1700, 40, 8, [OP.H2O]), (1700, 27, 16, [OP.H2O]), (2100, 32, 8, [OP.SNAPKV, OP.H2O]),
+                                          (2300, 27, 32, [OP.SNAPKV]), (800, 32, 32, [OP.SNAPKV, OP.H2O])],
+                         ids=["two_tiles_h2o", "two_heads_h2o", "one_tile", "padded_window", "whole_tiles"])
+def test_jobs_just_past_a_wave_stay_in_the_pipelined_kernel(L, w, hq, rules):
+    """520 jobs, eight more than the window kernels have resident, of more slices than these are the faster ones for:
+    the long-run form of the pipelined kernel, with padded rows and empty row tiles too."""
+    import paper_2606_15157_amd as rkv
+    layers = [[gen(34, s, l, L, w=w, Hq=hq, Hkv=8) for s in range(5)] for l in range(13)]
+    rkv.profile_enable(rkv.STAGE_ZERO)   # the pipelined kernel's preparation; the window kernels have none
+    try:
+        run_case((rules * 13)[:13], [w + 40] * 13, layers, window=w, label=f"past_L{L}_w{w}")
+        launches, _ = rkv.profile_read()
+    finally:
+        rkv.profile_enable(-1)
+    assert launches == 1
 
 
 @pytest.mark.parametrize("L,w,hq,hkv", [(3331, 27, 16, 8), (1024, 32, 32, 8)], ids=["padded", "few_slices"])
