@@ -172,8 +172,10 @@ __global__ __launch_bounds__(256, 2) void fullspan_cols_kernel(const PrefillLaun
     sCol[kg][kl] = sum;
     tile_barrier();
     if (kg > 0) return;
+    double total = (double)sum;   // rounded once, whatever the number of groups
 #pragma unroll
-    for (int k = 1; k < KG; ++k) sum += sCol[k][kl];
+    for (int k = 1; k < KG; ++k) total += (double)sCol[k][kl];
+    sum = (float)total;
   }
   if (j0 + kl < L) P.S[(size_t)job * L + j0 + kl] = sum * (1.f / (float)G);
 }
