@@ -241,7 +241,7 @@ int rkv_prefill_workspace_size(const rkv_plan* plan, const rkv_shape* shape, siz
  * this happens is rescored exactly on the device before selection (RKV_STATUS_REPAIRED; outputs
  * valid); an H2O_FULL layer reports RKV_STATUS_INVALID.  TOVA is exact by construction (per-head
  * running maxima).  Sums are 32-bit in a fixed order, so a call repeated on the same inputs gives the
- * same bits; which kernel scores a job depends on the whole call (jobs, prompt length, alignment), so
+ * same bits; which kernel scores a job depends on the whole call (jobs, rules, prompt length, alignment), so
  * the same sequence in a call of other layers or sequences may differ in the last bits of its scores,
  * and in the order of positions whose scores differ by no more than that.
  * The status word (rkv_prefill_check) must be clean of RKV_STATUS_TIMEOUT and
